@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 
 #include "su2_device.h"
@@ -298,12 +299,16 @@ hipError_t launch_test_links(const float *V, int64_t n, float beta, uint64_t see
 
 // ------------------------------------------------------- learned proposal
 constexpr int kNNParams = 2671;
-constexpr int kNNActRows = 176;  // per-sample record rows of the backward pass
+constexpr int kNNPart = kNNParams + 1;  // a workgroup's partial sums: gradient, loss
+constexpr int kNNTile = 64;             // samples a workgroup takes at a time
+// Workgroups of a training step: one per 64 samples, at most 512 (two per CU,
+// 12 MB of partial sums), which then take several tiles each.
+inline int nn_parts(int batch) { return std::min((batch - 1) / kNNTile + 1, 512); }
 
 struct NNBuffers {
     float *params, *grad, *m, *v;  // kNNParams each
     float *alpha, *a0;             // training data
-    float *act, *loss;             // kNNActRows x batch, batch
+    double *part;                  // nn_parts(batch) x kNNPart partial sums of a step
     float *table;                  // kNNRows x kNNRow, kNNTablePad floats into table_alloc
     float *table_alloc;
 };
@@ -312,9 +317,9 @@ hipError_t launch_nn_data(float *alpha, float *a0, int64_t n, float lo, float hi
                           hipStream_t stream);
 // Forward/backward of samples [offset, offset + batch) (mod n) and the
 // gradient of the mean NLL into nb.grad; mean loss into *loss_out if given.
+// step > 0: the parameters then take Adam step number `step` at rate lr.
 hipError_t launch_nn_step(const NNBuffers &nb, int64_t offset, int batch, int64_t n,
-                          double *loss_out, hipStream_t stream);
-hipError_t launch_nn_adam(const NNBuffers &nb, float lr, int step, hipStream_t stream);
+                          double *loss_out, float lr, int step, hipStream_t stream);
 hipError_t launch_nn_table(const float *params, float *table, hipStream_t stream);
 hipError_t launch_test_learned(const float *table, const float *V, const float *Uold, int64_t n,
                                float beta, uint64_t seed, uint32_t sweep, uint32_t mu,

@@ -1128,7 +1128,7 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
 struct su2_nn {
     NNBuffers b;
     int64_t ndata = 0;     // training samples held
-    int64_t act_cap = 0;   // batch capacity of the per-sample record
+    int part_cap = 0;      // workgroups b.part holds partial sums of
     int step = 0;          // Adam step counter
     bool table_ready = false;
     hipStream_t stream = nullptr;
@@ -2074,12 +2074,12 @@ int su2_test_gauge_transform(su2_ctx *c, uint64_t seed)
 
 static void nn_free(su2_nn *n)
 {
-    // b.a0 lives inside the b.alpha allocation and b.loss inside b.act
-    // (b.table points kNNTablePad floats into b.table_alloc)
-    float *bufs[] = {n->b.params, n->b.grad, n->b.m, n->b.v, n->b.alpha, n->b.act,
-                     n->b.table_alloc};
+    // b.a0 lives inside the b.alpha allocation (b.table points kNNTablePad
+    // floats into b.table_alloc)
+    float *bufs[] = {n->b.params, n->b.grad, n->b.m, n->b.v, n->b.alpha, n->b.table_alloc};
     for (float *p : bufs)
         if (p) (void)hipFree(p);
+    if (n->b.part) (void)hipFree(n->b.part);
     if (n->dev_loss) (void)hipFree(n->dev_loss);
 }
 
@@ -2229,17 +2229,17 @@ int su2_nn_get_data(su2_nn *n, int64_t *count, float *alpha_host, float *a0_host
     SU2_API_END
 }
 
-static int nn_reserve_act(su2_nn *n, int batch)
+static int nn_reserve_part(su2_nn *n, int batch)
 {
-    if (batch <= n->act_cap) return SU2_OK;
-    if (n->b.act) (void)hipFree(n->b.act);
-    n->b.act = n->b.loss = nullptr;
-    n->act_cap = 0;
+    const int parts = nn_parts(batch);
+    if (parts <= n->part_cap) return SU2_OK;
+    if (n->b.part) (void)hipFree(n->b.part);
+    n->b.part = nullptr;
+    n->part_cap = 0;
     void *p = nullptr;
-    HIP_TRY(hipMalloc(&p, (size_t)batch * (kNNActRows + 1) * sizeof(float)));
-    n->b.act = static_cast<float *>(p);
-    n->b.loss = n->b.act + (size_t)batch * kNNActRows;
-    n->act_cap = batch;
+    HIP_TRY(hipMalloc(&p, (size_t)parts * kNNPart * sizeof(double)));
+    n->b.part = static_cast<double *>(p);
+    n->part_cap = parts;
     return SU2_OK;
 }
 
@@ -2248,7 +2248,7 @@ int su2_nn_loss_grad(su2_nn *n, int64_t offset, int32_t batch, double *loss, flo
     SU2_API_BEGIN
     if (!n || batch <= 0 || offset < 0) return fail(SU2_EINVAL, "bad arguments");
     if (!n->ndata) return fail(SU2_ESTATE, "no training data");
-    int rc = nn_reserve_act(n, batch);
+    int rc = nn_reserve_part(n, batch);
     if (rc) return rc;
     if (n->loss_cap < 1) {
         void *p = nullptr;
@@ -2256,7 +2256,8 @@ int su2_nn_loss_grad(su2_nn *n, int64_t offset, int32_t batch, double *loss, flo
         n->dev_loss = static_cast<double *>(p);
         n->loss_cap = 1;
     }
-    HIP_TRY(launch_nn_step(n->b, offset % n->ndata, batch, n->ndata, n->dev_loss, n->stream));
+    HIP_TRY(launch_nn_step(n->b, offset % n->ndata, batch, n->ndata, n->dev_loss, 0.0f, 0,
+                           n->stream));
     HIP_TRY(hipStreamSynchronize(n->stream));
     if (loss) HIP_TRY(hipMemcpy(loss, n->dev_loss, sizeof(double), hipMemcpyDeviceToHost));
     if (grad_host)
@@ -2283,7 +2284,7 @@ static int nn_train_steps(su2_nn *n, int32_t steps, int32_t batch, const LRSched
                           double *loss_history_host)
 {
     if (!n->ndata) return fail(SU2_ESTATE, "no training data");
-    int rc = nn_reserve_act(n, batch);
+    int rc = nn_reserve_part(n, batch);
     if (rc) return rc;
     if (n->loss_cap < steps) {
         if (n->dev_loss) (void)hipFree(n->dev_loss);
@@ -2297,8 +2298,8 @@ static int nn_train_steps(su2_nn *n, int32_t steps, int32_t batch, const LRSched
     int64_t offset = 0;
     for (int32_t t = 0; t < steps; ++t) {
         HIP_TRY(launch_nn_step(n->b, offset, batch, n->ndata,
-                               loss_history_host ? n->dev_loss + t : nullptr, n->stream));
-        HIP_TRY(launch_nn_adam(n->b, (float)sched.at(t), ++n->step, n->stream));
+                               loss_history_host ? n->dev_loss + t : nullptr,
+                               (float)sched.at(t), ++n->step, n->stream));
         offset = (offset + batch) % n->ndata;
     }
     n->table_ready = false;

@@ -284,3 +284,27 @@ def test_proposal_cannot_be_destroyed_while_attached(su2):
         lat.close()
     # net was destroyed by the context manager: nothing held it any more
     assert net.h is None
+
+
+# edges of the training kernel's tiles (16 samples a wave, 64 a workgroup), the
+# wrap of the data under a minibatch, and more tiles than workgroups (512 x 64)
+@pytest.mark.parametrize("batch,ndata,offset", [(1, 5, 3), (15, 40, 30), (17, 17, 0), (64, 64, 5),
+                                                (65, 100, 99), (32768 + 33, 30011, 30000)])
+def test_gradient_at_tile_edges_matches_oracle(su2, batch, ndata, offset):
+    announce(f"nn gradient tiles batch={batch} ndata={ndata} offset={offset}")
+    p = random_params(7)
+    al = inputs.log_uniform(ndata, 0.5, 30.0, 8).astype(np.float32)
+    x = np.random.default_rng(9).uniform(-0.999, 0.999, ndata).astype(np.float32)
+    with su2.NN(params=p) as net:
+        net.set_data(al, x)
+        loss, g = net.loss_grad(offset, batch)
+        again, g2 = net.loss_grad(offset, batch)
+    assert loss == again and np.array_equal(g, g2)  # fixed summation order
+    i = (offset + np.arange(batch)) % ndata
+    wl, wg = nn.loss_and_grad(p.astype(np.float64), al[i].astype(np.float64),
+                              x[i].astype(np.float64))
+    assert loss == pytest.approx(wl, rel=1e-5)
+    for lo, hi in ((0, 32), (32, 64), (64, 1088), (1088, 1120), (1120, 2624), (2624, 2671)):
+        w = wg[lo:hi]
+        bound = 1e-3 * np.abs(w) + 1e-4 * np.linalg.norm(w)
+        assert np.all(np.abs(g[lo:hi] - w) <= bound), (lo, hi)
