@@ -95,7 +95,8 @@ int su2_init_ext(su2_ctx **out, const int32_t dims[4], double beta, uint64_t see
  * (1/2) Tr[L_mu(s,R) L_nu(s+R mu,T) L_mu(s+T nu,R)^+ L_nu(s,T)^+], with
  * L_mu(x, n) = U_mu(x) U_mu(x+mu) ... U_mu(x+(n-1)mu), R = 1..rmax,
  * T = 1..tmax; W(1,1) is the plaquette.  Per-site values FP32, sums FP64
- * (deterministic order).  Synchronous; allocates a temporary device buffer.
+ * (deterministic order).  Synchronous; the first call allocates a device
+ * buffer of 160 KB that the context keeps.
  * SU2_EINVAL unless 1 <= rmax, tmax <= 4 and both are below every extent;
  * SU2_ESTATE on an FP64 context.  out: host double[rmax * tmax]. */
 int su2_wilson_loops(su2_ctx *ctx, int rmax, int tmax, double *out);

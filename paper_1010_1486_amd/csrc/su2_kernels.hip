@@ -717,20 +717,35 @@ __global__ __launch_bounds__(1024) void small_sweeps_kernel(const Rep *__restric
 }
 
 // ---------------------------------------------------------- Wilson loops
-// W(R, T) of the rectangle R along mu, T along nu at site s, for the 12
-// ordered planes: (1/2)Tr[A_R C_T (B_T D_T)^+] = qdot(A_R C_T, B_T D_T) with
-// A_R = L_mu(s, R), C_T = L_nu(s + R mu, T), B_T = L_nu(s, T),
-// D_T = L_mu(s + T nu, R), L_mu(x, n) = U_mu(x) ... U_mu(x + (n - 1) mu).
-// The lines are extended one link at a time (R outer, T inner), so a plane
-// costs R + T + 2RT link loads for all R, T <= N.  One thread per site (both
-// parities) and plane; per-site values FP32, the sum over a workgroup FP64
-// into part[slot * N * N + (R - 1) N + (T - 1)], slot = plane * blocks + block.
+// W(R, T) of the rectangle R along mu, T along nu at site s: (1/2)Tr[A_R C_T
+// (B_T D_T)^+] = qdot(A_R C_T, B_T D_T) with A_R = L_mu(s, R), C_T =
+// L_nu(s + R mu, T), B_T = L_nu(s, T), D_T = L_mu(s + T nu, R),
+// L_mu(x, n) = U_mu(x) ... U_mu(x + (n - 1) mu).  The lines are extended one
+// link at a time (R outer, T inner), so a plane costs R + T + 2RT link loads
+// for all R, T <= N.  The rectangle R x T of the plane (nu, mu) is the
+// rectangle T x R of (mu, nu) walked the other way round, with the same value
+// bit for bit, so the six planes mu < nu give the sum over all twelve ordered
+// ones: each loop adds to the sizes R x T and T x R.
+//
+// A workgroup walks units of 256 sites and one plane; consecutive units of an
+// XCD are the six planes of one set of sites, then the next set, so the sites'
+// links come from that XCD's L2.  Half the waves take the even and half the
+// odd sites of the same 128 half-sites, because neighbours alternate parity.
+// Per-site values are FP32; every thread adds its own in FP64 over all its
+// units and the workgroup's sums go to part[workgroup][pair (R, T), R <= T].
+//
+// Bound: L2 gathers (40 loads of 16 bytes per site and plane at N = 4, 15.7
+// TB/s at 48^4) and VALU (62 quaternion products of 16 operations).  A W(4, 4)
+// measurement takes 1303 us at 48^4 and 245 us at 32^4; with twelve planes, a
+// workgroup sum per plane and a buffer allocated on each call it took 4266 and
+// 806 us.
+constexpr int kWilsonGrid = 768;  // workgroups: the three a CU holds (138 VGPRs)
 
 // Site-index offset of k steps along a direction from coordinate c (extent n,
-// canonical stride st), periodic for any k >= 0.
+// canonical stride st), periodic for 0 <= k <= n.
 __device__ __forceinline__ int32_t step_off(int c, int k, int n, int32_t st)
 {
-    return ((c + k) % n - c) * st;
+    return (k - (c + k >= n ? n : 0)) * st;
 }
 
 __device__ __forceinline__ int pick4(int a, int v0, int v1, int v2, int v3)
@@ -738,25 +753,42 @@ __device__ __forceinline__ int pick4(int a, int v0, int v1, int v2, int v3)
     return a == 0 ? v0 : a == 1 ? v1 : a == 2 ? v2 : v3;
 }
 
-// grid (blocks over the V sites, 12 ordered planes): one thread per site and
-// plane, partial sums per (plane, workgroup).
-template <int N>
-__global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ reps, int rmax,
-                                                     int tmax, double *__restrict__ part)
+// Index of the size pair {r, t} (0-based, any order) among r <= t < N.
+__host__ __device__ constexpr int wilson_pair(int r, int t)
 {
+    const int a = r < t ? r : t, b = r < t ? t : r;
+    return b * (b + 1) / 2 + a;
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ reps,
+                                                     double *__restrict__ part)
+{
+    constexpr int NP = N * (N + 1) / 2;
     const Rep &R = reps[0];
     const Geom &g = R.g;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const int o = (int)blockIdx.y, mu = o / 3, nu = o % 3 < mu ? o % 3 : o % 3 + 1;
-    float w[N][N];
+    const uint32_t nsets = (g.vh + 127u) / 128u;  // sets of 128 half-sites
+    const uint32_t per = (nsets + 7u) / 8u;       // sets per XCD
+    const uint32_t x = blockIdx.x & 7u, step = gridDim.x >> 3;
+    const int par = threadIdx.x >= 128u ? 1 : 0;
+    double acc[NP];
 #pragma unroll
-    for (int r = 0; r < N; ++r)
-#pragma unroll
-        for (int t = 0; t < N; ++t) w[r][t] = 0.0f;
-    if (i < 2u * g.vh) {
-        const int par = i >= g.vh ? 1 : 0;
+    for (int i = 0; i < NP; ++i) acc[i] = 0.0;
+    for (uint32_t u = blockIdx.x >> 3; u < 6u * per; u += step) {
+        const uint32_t set = x * per + u / 6u;
+        const int o = (int)(u % 6u);  // plane mu < nu: 01 02 03 12 13 23
+        const int mu = o < 3 ? 0 : o < 5 ? 1 : 2, nu = o < 3 ? o + 1 : o < 5 ? o - 1 : 3;
+        const uint32_t h = set * 128u + (threadIdx.x & 127u);
+        if (set >= nsets || h >= g.vh) continue;
         int c0[4];
-        decode(g, par ? i - g.vh : i, par, c0[0], c0[1], c0[2], c0[3]);
+        {
+            const uint32_t zt = fdiv(h, g.m_P, g.s_P), r = h - zt * g.P;
+            const uint32_t y = fdiv(r, g.m_hx, g.s_hx);
+            c0[1] = (int)y;
+            c0[3] = (int)(zt / (uint32_t)g.nz);
+            c0[2] = (int)zt - c0[3] * g.nz;
+            c0[0] = 2 * (int)(r - y * g.hx) + ((par + c0[1] + c0[2] + c0[3]) & 1);
+        }
         const int32_t sy = g.nx, sz = g.nx * g.ny, stt = g.nx * g.ny * g.nz;
         // canonical index of the site; the link k steps along mu and l along nu
         // from it lies at s0 + oa[k] + ob[l] and has parity par + k + l
@@ -780,22 +812,17 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ rep
 #define SU2_WL(A, k, l) ld(A[((k) + (l)) & 1], (s0 + (uint32_t)(oa[k] + ob[l])) >> 1)
         // every size up to N x N is computed without branches, so that the loads
         // can be issued ahead of the products; sizes beyond (rmax, tmax) are not
-        // reported (the offsets wrap periodically, so every load stays inside)
-        // the links of each stage are loaded together (the scheduling barrier
+        // reported (the offsets wrap periodically, so every load stays inside).
+        // The links of each stage are loaded together (the scheduling barrier
         // keeps them ahead of the products that use them)
-        const Q one{1.0f, 0.0f, 0.0f, 0.0f};
         Q B[N], D[N], L[2 * N + 1];
 #pragma unroll
         for (int t = 0; t < N; ++t) L[t] = SU2_WL(Anu, 0, t);
         __builtin_amdgcn_sched_barrier(0);
-        Q P = one;
+        B[0] = L[0];
 #pragma unroll
-        for (int t = 0; t < N; ++t) {
-            P = qmul(P, L[t]);
-            B[t] = P;
-            D[t] = one;
-        }
-        Q A = one;
+        for (int t = 1; t < N; ++t) B[t] = qmul(B[t - 1], L[t]);
+        Q A;
 #pragma unroll
         for (int r = 0; r < N; ++r) {
             L[2 * N] = SU2_WL(Amu, r, 0);
@@ -805,40 +832,42 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ rep
                 L[2 * t + 1] = SU2_WL(Anu, r + 1, t);
             }
             __builtin_amdgcn_sched_barrier(0);
-            A = qmul(A, L[2 * N]);
-            Q C = one;
+            A = r ? qmul(A, L[2 * N]) : L[2 * N];
+            Q C;
 #pragma unroll
             for (int t = 0; t < N; ++t) {
-                D[t] = qmul(D[t], L[2 * t]);
-                C = qmul(C, L[2 * t + 1]);
-                w[r][t] = qdot(qmul(A, C), qmul(B[t], D[t]));
+                D[t] = r ? qmul(D[t], L[2 * t]) : L[2 * t];
+                C = t ? qmul(C, L[2 * t + 1]) : L[2 * t + 1];
+                const double w = (double)qdot(qmul(A, C), qmul(B[t], D[t]));
+                // R x R stands for both orders of the plane
+                acc[wilson_pair(r, t)] += r == t ? 2.0 * w : w;
             }
         }
-        (void)rmax;
-        (void)tmax;
 #undef SU2_WL
     }
-    const uint32_t slot = blockIdx.y * gridDim.x + blockIdx.x;
 #pragma unroll
-    for (int r = 0; r < N; ++r)
-#pragma unroll
-        for (int t = 0; t < N; ++t) {
-            const double bs = block_sum((double)w[r][t]);
-            if (threadIdx.x == 0) part[(size_t)slot * N * N + r * N + t] = bs;
-        }
+    for (int i = 0; i < NP; ++i) {
+        const double bs = block_sum(acc[i]);
+        if (threadIdx.x == 0) part[(size_t)blockIdx.x * NP + i] = bs;
+    }
 }
 
-// Workgroup k: the sum of partial k over all slots in a fixed order (thread j
-// takes slots j, j + 256, ... in turn, then the fixed-order block sum).
+// Workgroup k: the sum of size pair k over all workgroups in a fixed order
+// (thread j takes partials j, j + 256, ... in turn, then the fixed-order block
+// sum), stored for R x T and T x R.
 __global__ __launch_bounds__(256) void wilson_sum_kernel(const double *__restrict__ part,
-                                                         uint32_t nslots, int nn,
+                                                         uint32_t nslots, int np,
                                                          double *__restrict__ out)
 {
     const int k = (int)blockIdx.x;
     double s = 0.0;
-    for (uint32_t b = threadIdx.x; b < nslots; b += blockDim.x) s += part[(size_t)b * nn + k];
+#pragma unroll 8
+    for (uint32_t b = threadIdx.x; b < nslots; b += blockDim.x) s += part[(size_t)b * np + k];
     s = block_sum(s);
-    if (threadIdx.x == 0) out[k] = s;
+    if (threadIdx.x) return;
+    for (int r = 0; r < kWilsonMax; ++r)
+        for (int t = 0; t < kWilsonMax; ++t)
+            if (wilson_pair(r, t) == k) out[r * kWilsonMax + t] = s;
 }
 
 // ------------------------------------------------------------- work queue
@@ -1352,16 +1381,35 @@ uint32_t queue_resident_grid(int block, bool learned)
     return (uint32_t)(per_cu * cus);
 }
 
-hipError_t launch_wilson(const Ens &e, int rmax, int tmax, double *part, double *sums,
-                         hipStream_t stream)
+// One workgroup per unit up to kWilsonGrid, a multiple of 8 for the XCD ranges.
+uint32_t wilson_grid(const Ens &e)
 {
-    const uint32_t nb = nblk(2ull * e.max_vh, 256);
-    hipLaunchKernelGGL(wilson_kernel<kWilsonMax>, dim3(nb, 12), dim3(256), 0, stream, e.reps,
-                       rmax, tmax, part);
+    const uint64_t units = 6ull * (((uint64_t)e.max_vh + 127) / 128 + 7);
+    return (uint32_t)std::min<uint64_t>(kWilsonGrid, (units + 7) & ~7ull);
+}
+
+size_t wilson_work_bytes()
+{
+    return ((size_t)kWilsonGrid * (kWilsonMax * (kWilsonMax + 1) / 2) + kWilsonMax * kWilsonMax) *
+           sizeof(double);
+}
+
+hipError_t launch_wilson(const Ens &e, int n, double *work, double **sums, hipStream_t stream)
+{
+    const dim3 grid(wilson_grid(e)), block(256);
+    double *const part = work + kWilsonMax * kWilsonMax;
+    *sums = work;
+    switch (n) {
+    case 4: hipLaunchKernelGGL(wilson_kernel<4>, grid, block, 0, stream, e.reps, part); break;
+    case 3: hipLaunchKernelGGL(wilson_kernel<3>, grid, block, 0, stream, e.reps, part); break;
+    default:
+        n = 2;
+        hipLaunchKernelGGL(wilson_kernel<2>, grid, block, 0, stream, e.reps, part);
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(wilson_sum_kernel, dim3(kWilsonMax * kWilsonMax), dim3(256), 0, stream,
-                       part, 12u * nb, kWilsonMax * kWilsonMax, sums);
+    const int np = n * (n + 1) / 2;
+    hipLaunchKernelGGL(wilson_sum_kernel, dim3(np), dim3(256), 0, stream, part, grid.x, np, work);
     return hipGetLastError();
 }
 

@@ -303,6 +303,7 @@ public:
     int n_or = 1;        // SU2_KP_OR: over-relaxation sweeps after each heat-bath sweep
     bool reunit_fused = false;  // reunitarise in the last pass stage of a reunitarisation sweep
     bool f64 = false;    // FP64 links (single lattice): the su2_f64.hip kernels
+    double *wilson_work = nullptr;  // partial sums of the Wilson loops (device, owned)
     uint2 *amap = nullptr;  // XCD-affine pass map (device, owned), see Ens
     uint32_t amap_len = 0;
     LaunchCfg cfg;
@@ -899,6 +900,8 @@ public:
         if (own_scratch && scratch) (void)hipFree(scratch);
         if (amap) (void)hipFree(amap);
         amap = nullptr;
+        if (wilson_work) (void)hipFree(wilson_work);
+        wilson_work = nullptr;
         if (own_stream && stream) (void)hipStreamDestroy(stream);
         pool = nullptr;
         scratch = nullptr;
@@ -1417,18 +1420,16 @@ int su2_wilson_loops(su2_ctx *c, int rmax, int tmax, double *out)
         tmax >= lmin)
         return fail(SU2_EINVAL, "rmax and tmax must be in [1, 4] and below every extent");
     if (E.f64) return fail(SU2_ESTATE, "Wilson loops are measured on FP32 links");
-    const Ens e = E.ens();
-    void *part = nullptr, *sums = nullptr;
-    HIP_TRY(hipMalloc(&part, (size_t)wilson_blocks(e) * kWilsonMax * kWilsonMax * 8));
-    hipError_t er = hipMalloc(&sums, kWilsonMax * kWilsonMax * 8);
-    double hs[kWilsonMax * kWilsonMax];
-    if (er == hipSuccess)
-        er = launch_wilson(e, rmax, tmax, (double *)part, (double *)sums, E.stream);
+    if (!E.wilson_work) {  // kept for the context's later measurements
+        void *p = nullptr;
+        HIP_TRY(hipMalloc(&p, wilson_work_bytes()));
+        E.wilson_work = static_cast<double *>(p);
+    }
+    double hs[kWilsonMax * kWilsonMax], *sums = nullptr;
+    hipError_t er = launch_wilson(E.ens(), std::max(rmax, tmax), E.wilson_work, &sums, E.stream);
     if (er == hipSuccess)
         er = hipMemcpyAsync(hs, sums, sizeof(hs), hipMemcpyDeviceToHost, E.stream);
     if (er == hipSuccess) er = hipStreamSynchronize(E.stream);
-    (void)hipFree(part);
-    if (sums) (void)hipFree(sums);
     if (er != hipSuccess) return fail(SU2_EHIP, std::string("wilson: ") + hipGetErrorString(er));
     if (int q = E.check_queue()) return q;
     const double norm = 12.0 * (double)volume_of(d);

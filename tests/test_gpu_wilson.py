@@ -44,3 +44,20 @@ def test_wilson_loops_cold_and_errors(su2):
         with pytest.raises(su2.SU2Error) as e:
             lat.wilson_loops(2, 2)
         assert e.value.code == su2.SU2_ESTATE
+
+
+@pytest.mark.parametrize("dims", [[4, 6, 6, 2], [14, 10, 6, 18]], ids=["1.1-sets", "59-sets"])
+def test_wilson_loops_reuse_their_buffer(su2, orc, dims):
+    """Sets of 128 half-sites with a ragged last one; measurements of other
+    sizes and other links in a row on one lattice."""
+    announce(f"wilson loops in a row dims={dims}")
+    lmin = min(dims)
+    with su2.Lattice(dims, 2.3, 1) as lat:
+        for k, (r, t) in enumerate(((4, 4), (2, 1), (3, 4), (1, 1))):
+            r, t = min(r, lmin - 1), min(t, lmin - 1)
+            links = inputs.random_links(dims, 60 + k, spread=0.6)
+            lat.set_links(links)
+            got = lat.wilson_loops(r, t)
+            np.testing.assert_array_equal(got, lat.wilson_loops(r, t))
+            want = orc.wilson_loops(dims, inputs.as_f64(links), r, t)
+            assert np.abs(got - want).max() < 1e-6, (k, np.abs(got - want).max())
