@@ -188,7 +188,8 @@ int su2_plaquette(su2_ctx *ctx, double *out);
 int su2_polyakov(su2_ctx *ctx, double *out_signed, double *out_abs);
 
 /* Copy links to / from the host exchange layout float[V][4][4] (host pointer,
- * 64*V bytes).  Synchronous. */
+ * 64*V bytes).  Synchronous.  The first call allocates a device staging
+ * buffer of at most 32 MB that the context keeps. */
 int su2_get_links(su2_ctx *ctx, float *host);
 int su2_set_links(su2_ctx *ctx, const float *host);
 

@@ -286,6 +286,11 @@ hipError_t launch_set_counter(const Ens &e, uint32_t sweep, uint32_t meas, int w
                               hipStream_t stream, QueueState *qs = nullptr);
 // results[R_COUNTS..] = proposals, accepts (as uint64); reset if asked.
 hipError_t launch_counts(const Ens &e, int reset, hipStream_t stream);
+// Sites [s0, s0 + n) of replica r between the device layout (dev64: FP64
+// links) and the host exchange layout (host64: double) in the device buffer
+// `stage`; set: into the links.
+hipError_t launch_exchange(const Ens &e, int r, bool dev64, bool host64, bool set, uint32_t s0,
+                           uint32_t n, void *stage, hipStream_t stream);
 hipError_t launch_gauge(const Ens &e, float *G, uint64_t seed, hipStream_t stream);
 // Streaming floor of a pass (single lattice): see stream_kernel.
 hipError_t launch_test_stream(const Ens &e, int mu, int par, float *out, hipStream_t stream);

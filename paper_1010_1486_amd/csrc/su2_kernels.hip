@@ -1140,6 +1140,38 @@ __global__ void gauge_apply_kernel(const Rep *__restrict__ reps, const float4 *_
     st(R.links, g.vh, mu, par, h, r);
 }
 
+// -------------------------------------------------------- host exchange
+// Sites [s0, s0 + n) of the link field (device layout, D components) to or
+// from the host exchange layout H[site][mu][c] in `stage`.  One thread per
+// link: a wave's stage accesses are contiguous and its class accesses are
+// runs of 8 links.  Bound: the copy over PCIe that follows or goes before
+// (17 GB/s to pageable host memory; the kernel moves its bytes at TB/s).
+template <typename D, typename H, bool SET>
+__global__ __launch_bounds__(256) void exchange_kernel(const Rep *__restrict__ reps, int r,
+                                                       uint32_t s0, uint32_t n,
+                                                       H *__restrict__ stage)
+{
+    const Rep &R = reps[r];
+    const Geom &g = R.g;
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 4ull * n) return;
+    const uint32_t s = s0 + (uint32_t)(i >> 2), mu = (uint32_t)i & 3u, h = s >> 1;
+    // extents are even, so the parity of a quotient is that of its coordinate
+    const uint32_t zt = fdiv(h, g.m_P, g.s_P), y = fdiv(h - zt * g.P, g.m_hx, g.s_hx);
+    const uint32_t par = ((s & 1u) + y + zt + zt / (uint32_t)g.nz) & 1u;
+    D *const cls = reinterpret_cast<D *>(R.links) + (size_t)(mu * 2u + par) * g.vh * 4u;
+    H *const out = stage + 4 * i;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        // FP64 links are two arrays of component pairs per class
+        D *const p = sizeof(D) == sizeof(double)
+                         ? cls + ((size_t)(k >> 1) * g.vh + h) * 2u + (k & 1)
+                         : cls + (size_t)h * 4u + k;
+        if (SET) *p = (D)out[k];
+        else out[k] = (H)*p;
+    }
+}
+
 // ---------------------------------------------------------- test hooks
 __global__ void test_philox_kernel(const uint32_t *__restrict__ ctr, int64_t n, uint32_t k0,
                                    uint32_t k1, uint32_t *__restrict__ out)
@@ -1306,6 +1338,30 @@ hipError_t launch_reunitarize(const Ens &e, hipStream_t stream)
     hipLaunchKernelGGL(reunit_kernel, dim3(nblk(e.max_vh, 256), 8, e.nrep), dim3(256), 0, stream,
                        e.reps);
     return hipGetLastError();
+}
+
+template <typename D, typename H>
+static hipError_t launch_exchange_as(const Ens &e, int r, bool set, uint32_t s0, uint32_t n,
+                                     void *stage, hipStream_t stream)
+{
+    const dim3 grid(nblk(4ull * n, 256)), block(256);
+    if (set)
+        hipLaunchKernelGGL((exchange_kernel<D, H, true>), grid, block, 0, stream, e.reps, r, s0, n,
+                           static_cast<H *>(stage));
+    else
+        hipLaunchKernelGGL((exchange_kernel<D, H, false>), grid, block, 0, stream, e.reps, r, s0,
+                           n, static_cast<H *>(stage));
+    return hipGetLastError();
+}
+
+hipError_t launch_exchange(const Ens &e, int r, bool dev64, bool host64, bool set, uint32_t s0,
+                           uint32_t n, void *stage, hipStream_t stream)
+{
+    if (dev64)
+        return host64 ? launch_exchange_as<double, double>(e, r, set, s0, n, stage, stream)
+                      : launch_exchange_as<double, float>(e, r, set, s0, n, stage, stream);
+    return host64 ? launch_exchange_as<float, double>(e, r, set, s0, n, stage, stream)
+                  : launch_exchange_as<float, float>(e, r, set, s0, n, stage, stream);
 }
 
 hipError_t launch_gauge(const Ens &e, float *G, uint64_t seed, hipStream_t stream)

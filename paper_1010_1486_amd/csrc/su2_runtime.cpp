@@ -73,22 +73,6 @@ using namespace su2rt;
         }                                                                               \
     } while (0)
 
-namespace {
-
-// Device position of component k of U_mu at half-site h of parity par: FP32
-// links are one array of V/2 float4 per class (mu * 2 + parity); FP64 links
-// two arrays of V/2 double pairs per class, (a0, a1) then (a2, a3).
-template <typename D>
-inline size_t dev_index(int mu, int par, int k, int64_t h, int64_t vh)
-{
-    if (sizeof(D) == sizeof(double))
-        return (((size_t)(mu * 2 + par) * 2u + (size_t)(k >> 1)) * (size_t)vh + (size_t)h) * 2u +
-               (size_t)(k & 1);
-    return ((size_t)(mu * 2 + par) * (size_t)vh + (size_t)h) * 4u + (size_t)k;
-}
-
-}  // namespace
-
 // Argument checks and the lattice geometry, shared with the SU(3) runtime.
 namespace su2rt {
 
@@ -303,6 +287,8 @@ public:
     int n_or = 1;        // SU2_KP_OR: over-relaxation sweeps after each heat-bath sweep
     bool reunit_fused = false;  // reunitarise in the last pass stage of a reunitarisation sweep
     bool f64 = false;    // FP64 links (single lattice): the su2_f64.hip kernels
+    void *stage = nullptr;          // staging of the host exchange (device, owned)
+    size_t stage_bytes = 0;
     double *wilson_work = nullptr;  // partial sums of the Wilson loops (device, owned)
     uint2 *amap = nullptr;  // XCD-affine pass map (device, owned), see Ens
     uint32_t amap_len = 0;
@@ -758,69 +744,51 @@ public:
         return SU2_OK;
     }
 
+    // Device staging of the host exchange: at most kStageBytes, kept for later
+    // calls; a smaller one where the device has no room for that.
+    static constexpr size_t kStageBytes = (size_t)32 << 20, kMinStage = 4096;
+    int reserve_stage(size_t want)
+    {
+        want = std::min(want, kStageBytes);
+        if (want <= stage_bytes) return SU2_OK;
+        if (stage) (void)hipFree(stage);  // no call leaves work on it
+        stage = nullptr;
+        stage_bytes = 0;
+        for (size_t b = want;; b /= 2) {
+            const hipError_t e = hipMalloc(&stage, b);
+            if (e == hipSuccess) {
+                stage_bytes = b;
+                return SU2_OK;
+            }
+            stage = nullptr;
+            (void)hipGetLastError();
+            if (b < 2 * kMinStage)
+                return fail(e == hipErrorOutOfMemory ? SU2_ENOMEM : SU2_EHIP,
+                            std::string("exchange staging buffer: ") + hipGetErrorString(e));
+        }
+    }
+
     // Host layout [t][z][y][x][mu][c] in H (float or double) <-> the device
-    // planes in the ensemble's precision.
-    template <typename D, typename H>
-    void gather(int r, const D *planes, H *host) const
+    // layout in the ensemble's precision, one staging buffer at a time.
+    template <typename H>
+    int exchange(int r, bool set, H *host)
     {
-        const int32_t *d = dims[r].data();
-        const int64_t V = volume_of(d), vh = V / 2;
-        for (int64_t s = 0; s < V; ++s) {
-            int64_t q = s;
-            const int x = (int)(q % d[0]);
-            q /= d[0];
-            const int y = (int)(q % d[1]);
-            q /= d[1];
-            const int z = (int)(q % d[2]);
-            const int t = (int)(q / d[2]);
-            const int par = (x + y + z + t) & 1;
-            for (int mu = 0; mu < 4; ++mu)
-                for (int k = 0; k < 4; ++k)
-                    host[(s * 4 + mu) * 4 + k] = (H)planes[dev_index<D>(mu, par, k, s >> 1, vh)];
+        const size_t V = (size_t)volume_of(dims[r].data()), site = 16 * sizeof(H);
+        if (!set)
+            if (int rc = check_queue()) return rc;
+        if (int rc = reserve_stage(V * site)) return rc;
+        const size_t chunk = stage_bytes / site;
+        for (size_t s0 = 0; s0 < V; s0 += chunk) {
+            const size_t n = std::min(chunk, V - s0);
+            if (set)
+                HIP_TRY_DRAIN(hipMemcpyAsync(stage, host + 16 * s0, n * site,
+                                             hipMemcpyHostToDevice, stream), stream);
+            HIP_TRY_DRAIN(launch_exchange(ens(), r, f64, sizeof(H) == sizeof(double), set,
+                                          (uint32_t)s0, (uint32_t)n, stage, stream), stream);
+            if (!set)
+                HIP_TRY_DRAIN(hipMemcpyAsync(host + 16 * s0, stage, n * site,
+                                             hipMemcpyDeviceToHost, stream), stream);
         }
-    }
-
-    template <typename D, typename H>
-    void scatter(int r, const H *host, D *planes) const
-    {
-        const int32_t *d = dims[r].data();
-        const int64_t V = volume_of(d), vh = V / 2;
-        for (int64_t s = 0; s < V; ++s) {
-            int64_t q = s;
-            const int x = (int)(q % d[0]);
-            q /= d[0];
-            const int y = (int)(q % d[1]);
-            q /= d[1];
-            const int z = (int)(q % d[2]);
-            const int t = (int)(q / d[2]);
-            const int par = (x + y + z + t) & 1;
-            for (int mu = 0; mu < 4; ++mu)
-                for (int k = 0; k < 4; ++k)
-                    planes[dev_index<D>(mu, par, k, s >> 1, vh)] = (D)host[(s * 4 + mu) * 4 + k];
-        }
-    }
-
-    template <typename D, typename H>
-    int get_links_as(int r, H *host)
-    {
-        const size_t n = (size_t)volume_of(dims[r].data()) * 16;
-        std::unique_ptr<D[]> planes(new (std::nothrow) D[n]);
-        if (!planes) return fail(SU2_ENOMEM, "host staging buffer of " + std::to_string(n * sizeof(D)) + " B");
-        HIP_TRY(hipMemcpyAsync(planes.get(), links[r], n * sizeof(D), hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipStreamSynchronize(stream));
-        if (int rc = check_queue()) return rc;
-        gather(r, planes.get(), host);
-        return SU2_OK;
-    }
-
-    template <typename D, typename H>
-    int set_links_as(int r, const H *host)
-    {
-        const size_t n = (size_t)volume_of(dims[r].data()) * 16;
-        std::unique_ptr<D[]> planes(new (std::nothrow) D[n]);
-        if (!planes) return fail(SU2_ENOMEM, "host staging buffer of " + std::to_string(n * sizeof(D)) + " B");
-        scatter(r, host, planes.get());
-        HIP_TRY(hipMemcpyAsync(links[r], planes.get(), n * sizeof(D), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         return SU2_OK;
     }
@@ -828,13 +796,13 @@ public:
     template <typename H>
     int get_links(int r, H *host)
     {
-        return f64 ? get_links_as<double>(r, host) : get_links_as<float>(r, host);
+        return exchange<H>(r, false, host);
     }
 
     template <typename H>
     int set_links(int r, const H *host)
     {
-        return f64 ? set_links_as<double>(r, host) : set_links_as<float>(r, host);
+        return exchange<H>(r, true, const_cast<H *>(host));  // only read
     }
 
     int set_sweep(uint32_t s)
@@ -902,6 +870,9 @@ public:
         amap = nullptr;
         if (wilson_work) (void)hipFree(wilson_work);
         wilson_work = nullptr;
+        if (stage) (void)hipFree(stage);
+        stage = nullptr;
+        stage_bytes = 0;
         if (own_stream && stream) (void)hipStreamDestroy(stream);
         pool = nullptr;
         scratch = nullptr;
