@@ -184,6 +184,9 @@ __host__ __device__ inline uint32_t queue_sweep_last(const QueuePlan &p, uint32_
 // Largest V/2 of the whole-sweep kernel (one workgroup per replica, up to
 // 1024 threads, 2 sites per thread).
 constexpr uint32_t kSmallMaxVh = 2048;
+// Largest V/2 whose heat-bath sweeps keep the field in LDS (three threads per
+// link, at most 960, and 208 bytes of LDS per half-site within 64 KiB).
+constexpr uint32_t kTinyMaxVh = 312;
 
 // Everything a launch needs to address an ensemble on the device.
 struct Ens {

@@ -9,6 +9,8 @@
 // class.  Plaquette and Polyakov sums are FP64 within a workgroup (wave
 // shuffles, then LDS) and 64-bit fixed point across workgroups, so every sum
 // is independent of scheduling order.
+#include <type_traits>
+
 #include "su2_internal.h"
 #include "su2_kcommon.h"
 
@@ -716,6 +718,330 @@ __global__ __launch_bounds__(1024) void small_sweeps_kernel(const Rep *__restric
     }
 }
 
+// ------------------------------------------------------ smallest lattices
+// Whole sweeps with the field in LDS (heat bath, V/2 <= kTinyMaxVh).  One
+// workgroup runs one replica, three threads a link: in stage 1 of a pass the
+// thread of role j computes the two staples of the j-th plane nu != mu; in
+// stage 2 role 0 adds them in plane order, draws and stores the link, while
+// roles 1 and 2 prepare the random numbers of the next pass (they depend on
+// no link): the first two trials of the a0 sampler up to the division by
+// alpha, and the direction.  Later trials, one link in some hundred, are drawn
+// in stage 2.  Every value is computed by the operations of the pass kernel,
+// so links and sums have its bits; sums are per-site fixed point as in
+// small_sweeps_kernel.
+//
+// Bound: latency of 16 dependent stages a sweep.  4^4 with both measurements
+// took 14.6 us a sweep with one thread a link and the field in memory.
+struct TinyRand {
+    // log2 r1 + cos^2(2 pi r2) log2 r3; r4^2; 1 - sqrt(r1) cos(2 pi r2); log2 r3
+    float g, r4s, dh, l3;
+};
+struct TinyDir {
+    float sth, cth, cph, sph;
+};
+
+__device__ __forceinline__ TinyRand tiny_trial(const U4 &w)
+{
+    const float r1 = u01(w.a), r2 = u01(w.b), r3 = u01(w.c), r4 = u01(w.d);
+    const float c = hw_cos_rev(r2), l3 = hw_log2(r3);
+    // the FMAs that sample_delta's expressions contract to
+    return TinyRand{fmaf(c * c, l3, hw_log2(r1)), r4 * r4, fmaf(-hw_sqrt(r1), c, 1.0f), l3};
+}
+
+__device__ __forceinline__ TinyDir tiny_direction(const U4 &w)
+{
+    float r5, r6;
+    dir_uniforms(w, r5, r6);
+    return TinyDir{2.0f * hw_sqrt(r5 * (1.0f - r5)), 1.0f - 2.0f * r5, hw_cos_rev(r6),
+                   hw_sin_rev(r6)};
+}
+
+// sample_delta's decision on one trial.
+__device__ __forceinline__ bool tiny_accept(const TinyRand &r, bool kp, float alpha,
+                                            float neg_ln2_over_alpha, float &d)
+{
+    if (kp) {
+        d = neg_ln2_over_alpha * r.g;
+        return r.r4s <= 1.0f - 0.5f * d;
+    }
+    d = r.dh;
+    return r.l3 <= alpha * -d * kLog2e;
+}
+
+// heatbath_link with the first two trials and the direction prepared.
+__device__ __forceinline__ Q tiny_heatbath(const Q &V, float beta, const TinyRand &t0,
+                                           const TinyRand &t1, const TinyDir &n, uint32_t site,
+                                           uint32_t sweep, uint32_t w2trial, uint32_t k0,
+                                           uint32_t k1)
+{
+    const float k2 = qdot(V, V);
+    const bool zero = !(k2 > 0.0f);
+    const float inv_k = zero ? 0.0f : hw_rsq(k2);
+    const float alpha = beta * k2 * inv_k;
+    const bool kp = alpha >= kKPMinAlpha;
+    const float nla = -kLn2 * hw_rcp(alpha);
+    float delta = 0.0f, d;
+    if (tiny_accept(t0, kp, alpha, nla, d) || tiny_accept(t1, kp, alpha, nla, d)) {
+        delta = d;
+    } else {
+        for (int t = 2; t < kTrialCap; ++t) {
+            const TinyRand r = tiny_trial(philox(site, sweep, w2trial, (uint32_t)t, k0, k1));
+            if (tiny_accept(r, kp, alpha, nla, d)) {
+                delta = d;
+                break;
+            }
+        }
+    }
+    const float amag = hw_sqrt(delta * (2.0f - delta));
+    const float as = amag * n.sth;
+    const Q X{1.0f - delta, as * n.cph, as * n.sph, amag * n.cth};
+    const Q Ut = zero ? Q{1.0f, 0.0f, 0.0f, 0.0f}
+                      : Q{V.w * inv_k, V.x * inv_k, V.y * inv_k, V.z * inv_k};
+    return qmul(X, qdag(Ut));
+}
+
+__device__ __forceinline__ Q lq(const float4 *p)
+{
+    const float4 v = *p;
+    return Q{v.x, v.y, v.z, v.w};
+}
+__device__ __forceinline__ float4 f4(const Q &q) { return float4{q.w, q.x, q.y, q.z}; }
+
+// A site's half-site neighbours, 16 bits each.
+struct TinySite {
+    uint32_t p[4], m[4];
+    uint32_t xodd;
+};
+
+__device__ __forceinline__ TinySite tiny_site(const Geom &g, uint32_t h, int par)
+{
+    PassSite s;
+    s.h = h;
+    decode(g, h, par, s.x, s.y, s.z, s.t);
+    const Deltas d = neighbour_deltas(g, s);
+    TinySite r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        r.p[i] = h + d.p[i];
+        r.m[i] = h + d.m[i];
+    }
+    r.xodd = (uint32_t)s.x & 1u;
+    return r;
+}
+
+// The two staples of plane (MU, nu), nu the J-th direction other than MU; F
+// holds class (mu, par) at F[(mu * 2 + par) * vh].
+template <int MU, int J>
+__device__ __forceinline__ Q tiny_staple(const float4 *F, uint32_t vh, int par, uint32_t h,
+                                         const TinySite &s)
+{
+    constexpr int nu = J + (J >= MU ? 1 : 0);
+    const float4 *const mo = F + (MU * 2 + (par ^ 1)) * vh;
+    const float4 *const np = F + (nu * 2 + par) * vh, *const no = F + (nu * 2 + (par ^ 1)) * vh;
+    return staple_pair(lq(no + s.p[MU]), lq(mo + s.p[nu]), lq(np + h),
+                       lq(np + (s.p[MU] + s.m[nu] - h)), lq(mo + s.m[nu]), lq(no + s.m[nu]));
+}
+
+template <int MU>
+__device__ __forceinline__ Q tiny_staple_role(int role, const float4 *F, uint32_t vh, int par,
+                                              uint32_t h, const TinySite &s)
+{
+    if (role == 0) return tiny_staple<MU, 0>(F, vh, par, h, s);
+    if (role == 1) return tiny_staple<MU, 1>(F, vh, par, h, s);
+    return tiny_staple<MU, 2>(F, vh, par, h, s);
+}
+
+// site_plaquettes of the site of parity PAR at half-site h.
+template <int PAR>
+__device__ __forceinline__ float tiny_plaquettes(const float4 *F, uint32_t vh, uint32_t h,
+                                                 const TinySite &s)
+{
+    const float4 *const own = F + PAR * vh, *const oth = F + (PAR ^ 1) * vh;
+    float sum = 0.0f;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+#pragma unroll
+        for (int nu = mu + 1; nu < 4; ++nu) {
+            const Q P = qmul(lq(own + 2 * mu * vh + h), lq(oth + 2 * nu * vh + s.p[mu]));
+            const Q Qq = qmul(lq(own + 2 * nu * vh + h), lq(oth + 2 * mu * vh + s.p[nu]));
+            sum += retr_adj(P, Qq);
+        }
+    return sum;
+}
+
+// flags: as small_sweeps_kernel.  vhp: V/2 of the largest replica rounded up
+// to whole waves; 3 vhp threads; dynamic LDS of tiny_lds(largest V/2) bytes.
+template <int MAXT>
+__global__ __launch_bounds__(MAXT) void tiny_sweeps_kernel(const Rep *__restrict__ reps, int nrep,
+                                                           int ns, uint32_t k0, uint32_t k1,
+                                                           int reunit_every, int flags,
+                                                           double *__restrict__ hist, uint32_t vhp)
+{
+    extern __shared__ float4 F[];
+    __shared__ unsigned long long sums[2][2][8];  // [sweep parity][plaquette, Polyakov][lane & 7]
+    const Rep &R = reps[blockIdx.x];
+    const Geom &g = R.g;
+    const uint32_t vh = g.vh, nthr = 3u * vhp;
+    float4 *const S = F + 8u * vh;      // staples of roles 1 and 2
+    float4 *const T = S + 2u * vh;      // random numbers: trial 0, trial 1, direction
+    // uniform over a wave (vhp is a multiple of 64)
+    const int role = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / vhp));
+    const uint32_t h = threadIdx.x - (uint32_t)role * vhp;
+    const bool live = h < vh;
+    const float beta = R.beta;
+    const uint32_t replica = R.replica;
+    float4 *const links = reinterpret_cast<float4 *>(R.links);
+    for (uint32_t i = threadIdx.x; i < 8u * vh; i += nthr) F[i] = links[i];
+    if (threadIdx.x < 32u) (&sums[0][0][0])[threadIdx.x] = 0ull;
+    const TinySite even = tiny_site(g, live ? h : 0u, 0), odd = tiny_site(g, live ? h : 0u, 1);
+    const uint32_t ns3 = (uint32_t)g.nx * g.ny * g.nz;
+    uint32_t sweep = R.cnt->sweep;  // written back by one thread at the end
+    uint32_t *const row_ctr = row_counter(R.cnt, (flags & 8) != 0);
+    uint32_t midx = *row_ctr;
+    const bool want_p = (flags & 1) != 0, want_l = (flags & 2) != 0;
+    const bool rows = (flags & 4) != 0 && hist != nullptr;
+
+    // random numbers of pass (mu, par) of sweep j (roles 1 and 2)
+    auto prepare = [&](uint32_t j, int mu, const TinySite &s) {
+        if (!live || role == 0) return;
+        const U4 w = philox(2u * h + s.xodd, j, word2((uint32_t)mu, TAG_TRIAL, replica),
+                            role == 1 ? 0u : 1u, k0, k1);
+        const TinyRand r = tiny_trial(w);
+        T[(role - 1) * vh + h] = float4{r.g, r.r4s, r.dh, r.l3};
+        if (role == 1) {
+            const TinyDir d = tiny_direction(w);
+            T[2u * vh + h] = float4{d.sth, d.cth, d.cph, d.sph};
+        }
+    };
+    // Polyakov loop of the configuration at the end of the sweep before (role 2)
+    auto polyakov = [&](uint32_t slot) {
+        if (role != 2) return;
+        for (uint32_t xs = h; xs < ns3; xs += vhp) {
+            const uint32_t x = xs % (uint32_t)g.nx, r = xs / (uint32_t)g.nx;
+            const uint32_t y = r % (uint32_t)g.ny, z = r / (uint32_t)g.ny;
+            const uint32_t pbase = (x + y + z) & 1u;
+            Q P{1.0f, 0.0f, 0.0f, 0.0f};
+            for (int t = 0; t < g.nt; ++t)
+                P = qmul(P, lq(F + (6u + ((pbase + (uint32_t)t) & 1u)) * vh + (xs >> 1) +
+                               (uint32_t)t * (ns3 >> 1)));
+            atomicAdd(&sums[slot][1][threadIdx.x & 7u], to_fixed((double)P.w));
+        }
+    };
+    // history row of the sweep before, whose sums are complete (one thread)
+    auto finish = [&](uint32_t slot) {
+        if (threadIdx.x != 2u * vhp) return;
+        unsigned long long tp = 0ull, tl = 0ull;
+        for (int i = 0; i < 8; ++i) {
+            tp += sums[slot][0][i];
+            tl += sums[slot][1][i];
+            sums[slot][0][i] = sums[slot][1][i] = 0ull;
+        }
+        const double p = want_p ? from_fixed(tp) / (12.0 * (double)vh) : 0.0;
+        const double l = want_l ? from_fixed(tl) / (double)ns3 : 0.0;
+        double *row = hist + 3 * ((size_t)midx * nrep + blockIdx.x);
+        row[0] = p;
+        row[1] = l;
+        row[2] = fabs(l);
+    };
+
+    // pass (mu, par) of sweep number i of the launch; s: this link's site, other:
+    // the site of the next pass
+    auto pass = [&](int i, int mu, auto PAR, const TinySite &s, const TinySite &other, bool fused) {
+        constexpr int par = decltype(PAR)::value;
+        const uint32_t slot = (uint32_t)i & 1u;
+        // With 960 threads (128 VGPRs a lane) the 144 LDS addresses of the staples
+        // must not be kept over the sweeps: hide that the class stride is constant
+        uint32_t stride = vh;
+        if constexpr (MAXT > 512) asm volatile("" : "+s"(stride));
+        // stage 1: the role's staples
+        Q st{0.0f, 0.0f, 0.0f, 0.0f};
+        TinyRand t0{}, t1{};
+        TinyDir dir{};
+        if (live) {
+            if (mu == 0) st = tiny_staple_role<0>(role, F, stride, par, h, s);
+            else if (mu == 1) st = tiny_staple_role<1>(role, F, stride, par, h, s);
+            else if (mu == 2) st = tiny_staple_role<2>(role, F, stride, par, h, s);
+            else st = tiny_staple_role<3>(role, F, stride, par, h, s);
+            if (role) {
+                S[(role - 1) * vh + h] = f4(st);
+            } else {
+                // taken over before roles 1 and 2 write the next pass's
+                const float4 a = T[h], b = T[vh + h], d = T[2u * vh + h];
+                t0 = TinyRand{a.x, a.y, a.z, a.w};
+                t1 = TinyRand{b.x, b.y, b.z, b.w};
+                dir = TinyDir{d.x, d.y, d.z, d.w};
+            }
+        }
+        __syncthreads();
+        // stage 2: the update; meanwhile the next pass's random numbers
+        if (role == 0) {
+            if (live) {
+                const Q zero{0.0f, 0.0f, 0.0f, 0.0f};
+                const Q s1 = lq(S + h), s2 = lq(S + vh + h);
+                const Q v0 = qadd(zero, st), v1 = qadd(v0, s1);
+                const Q Un = tiny_heatbath(qadd(v1, s2), beta, t0, t1, dir,
+                                           2u * h + s.xodd, sweep,
+                                           word2((uint32_t)mu, TAG_TRIAL, replica), k0, k1);
+                F[(mu * 2 + par) * vh + h] = f4(Un);
+                if (fused && par == 1 && mu > 0) {
+                    // staples of the planes nu < mu
+                    const Q Vlow = mu == 1 ? v0 : mu == 2 ? v1 : qadd(v1, s2);
+                    atomicAdd(&sums[slot][0][threadIdx.x & 7u],
+                              to_fixed((double)retr(Un, Vlow)));
+                }
+            }
+        } else {
+            const bool last = mu == 3 && par == 1;
+            prepare(last ? sweep + 1u : sweep, last ? 0 : par ? mu + 1 : mu, other);
+            // what is left of the sweep before: U_3 keeps its values until mu = 3
+            if (rows && i > 0 && mu == 0) {
+                if (par == 0) {
+                    if (want_l) polyakov(slot ^ 1u);
+                } else {
+                    finish(slot ^ 1u);
+                    ++midx;
+                }
+            }
+        }
+        __syncthreads();
+    };
+
+    prepare(sweep, 0, even);
+    __syncthreads();
+    for (int i = 0; i < ns; ++i, ++sweep) {
+        const bool reunit = reunit_every > 0 && ((sweep + 1u) % (uint32_t)reunit_every) == 0u;
+        const uint32_t slot = (uint32_t)i & 1u;
+        const bool fused = want_p && !reunit;
+        for (int mu = 0; mu < 4; ++mu) {
+            pass(i, mu, std::integral_constant<int, 0>{}, even, odd, fused);
+            pass(i, mu, std::integral_constant<int, 1>{}, odd, even, fused);
+        }
+        if (reunit) {
+            for (uint32_t j = threadIdx.x; j < 8u * vh; j += nthr) F[j] = f4(unit_q(lq(F + j)));
+            __syncthreads();
+            if (want_p && live && role < 2) {
+                const float sum = role ? tiny_plaquettes<1>(F, vh, h, odd)
+                                       : tiny_plaquettes<0>(F, vh, h, even);
+                atomicAdd(&sums[slot][0][threadIdx.x & 7u], to_fixed((double)sum));
+            }
+            __syncthreads();  // the next sweep writes the links these plaquettes read
+        }
+    }
+    if (rows && ns > 0) {
+        const uint32_t slot = (uint32_t)(ns - 1) & 1u;
+        if (want_l) polyakov(slot);
+        __syncthreads();
+        finish(slot);
+        ++midx;
+    }
+    for (uint32_t i = threadIdx.x; i < 8u * vh; i += nthr) links[i] = F[i];
+    __syncthreads();  // every thread has read the counters before they change
+    if (threadIdx.x == 2u * vhp) {
+        R.cnt->sweep = sweep;
+        *row_ctr = midx;
+    }
+}
+
 // ---------------------------------------------------------- Wilson loops
 // W(R, T) of the rectangle R along mu, T along nu at site s: (1/2)Tr[A_R C_T
 // (B_T D_T)^+] = qdot(A_R C_T, B_T D_T) with A_R = L_mu(s, R), C_T =
@@ -1373,10 +1699,28 @@ hipError_t launch_gauge(const Ens &e, float *G, uint64_t seed, hipStream_t strea
     return hipGetLastError();
 }
 
+// LDS of the in-LDS sweeps: 8 classes, 2 staples and 3 random-number records
+// of 16 bytes per half-site.
+static constexpr uint32_t tiny_lds(uint32_t vh) { return 13u * 16u * vh; }
+static_assert(tiny_lds(kTinyMaxVh) + 256 <= 65536, "64 KiB of LDS per workgroup");
+
 hipError_t launch_small_sweeps(const Ens &e, int ns, uint64_t seed, int reunit_every, int flags,
                                double *hist, const float *table, hipStream_t stream)
 {
     if (ns <= 0) return hipSuccess;
+    if (!table && e.max_vh <= kTinyMaxVh) {
+        const uint32_t vhp = (e.max_vh + 63u) & ~63u;
+        const dim3 grid(e.nrep), tiny(3u * vhp);
+        if (tiny.x <= 384u)
+            hipLaunchKernelGGL(tiny_sweeps_kernel<384>, grid, tiny, tiny_lds(e.max_vh), stream,
+                               e.reps, e.nrep, ns, lo32(seed), hi32(seed), reunit_every, flags, hist,
+                               vhp);
+        else
+            hipLaunchKernelGGL(tiny_sweeps_kernel<960>, grid, tiny, tiny_lds(e.max_vh), stream,
+                               e.reps, e.nrep, ns, lo32(seed), hi32(seed), reunit_every, flags, hist,
+                               vhp);
+        return hipGetLastError();
+    }
     const uint32_t block = std::min<uint32_t>(1024u, (e.max_vh + 63u) & ~63u);
     if (table)
         hipLaunchKernelGGL(small_sweeps_kernel<true>, dim3(e.nrep), dim3(block), 0, stream, e.reps,
