@@ -28,6 +28,7 @@ constexpr int kNumAcc = 4;  // plaquette, Polyakov (fixed point); proposals, acc
 constexpr size_t kAccBytes = (size_t)kNumAcc * kBuckets * kBucketStride * 8;
 
 enum Result { R_PLAQ = 0, R_POLY_SIGNED = 1, R_POLY_ABS = 2, R_COUNTS = 4 };
+constexpr int kResultSlots = 8;
 enum Acc { ACC_PLAQ = 0, ACC_POLY = 1, ACC_PROPOSED = 2, ACC_ACCEPTED = 3 };
 
 struct Counters {
@@ -76,7 +77,7 @@ struct Rep {
 };
 
 // Per-replica scratch: counters, accumulators, result slots.
-constexpr size_t kRepScratch = sizeof(Counters) + kAccBytes + 8 * sizeof(double);
+constexpr size_t kRepScratch = sizeof(Counters) + kAccBytes + kResultSlots * sizeof(double);
 
 struct LaunchCfg {
     int pass_block = 256;

@@ -321,9 +321,12 @@ public:
         return align_up(blocks * 4, 256);
     }
     static size_t rep_bytes() { return align_up(kRepScratch, 256); }
+    // A batch's result slots lie side by side behind the replicas' scratch, so
+    // that the host reads them in one copy; a single lattice's are in its own.
+    static size_t results_bytes(int n) { return n > 1 ? (size_t)n * kResultSlots * 8 : 0; }
     static size_t scratch_need(int n, const std::vector<std::array<int32_t, 4>> &d)
     {
-        return descr_bytes(n) + 2 * bmap_bytes(n, d) + (size_t)n * rep_bytes();
+        return descr_bytes(n) + 2 * bmap_bytes(n, d) + (size_t)n * rep_bytes() + results_bytes(n);
     }
 
     Rep *d_reps() const { return reinterpret_cast<Rep *>(scratch); }
@@ -344,7 +347,18 @@ public:
     }
     double *results(int r) const
     {
+        if (n > 1) return reinterpret_cast<double *>(rep_scratch(n)) + (size_t)r * kResultSlots;
         return reinterpret_cast<double *>(rep_scratch(r) + sizeof(Counters) + kAccBytes);
+    }
+
+    // Every replica's result slots, once the stream has written them.
+    int read_results(std::vector<double> &v)
+    {
+        v.resize((size_t)n * kResultSlots);
+        HIP_TRY_DRAIN(hipMemcpyAsync(v.data(), results(0), v.size() * sizeof(double),
+                                     hipMemcpyDeviceToHost, stream), stream);
+        HIP_TRY(hipStreamSynchronize(stream));
+        return SU2_OK;
     }
 
     Ens ens() const
@@ -715,16 +729,14 @@ public:
         if (flags & 1) HIP_TRY(plaquette_launch());
         if (flags & 2) HIP_TRY(polyakov_launch());
         HIP_TRY(launch_take(ens(), flags, stream));
-        std::vector<double> v(3 * (size_t)n);
-        for (int r = 0; r < n; ++r)
-            HIP_TRY_DRAIN(hipMemcpyAsync(&v[3 * r], results(r), 3 * sizeof(double),
-                                         hipMemcpyDeviceToHost, stream), stream);
-        HIP_TRY(hipStreamSynchronize(stream));
+        std::vector<double> v;
+        if (int rc = read_results(v)) return rc;
         if (int rc = check_queue()) return rc;
         for (int r = 0; r < n; ++r) {
-            if (plaq) plaq[r] = v[3 * r + R_PLAQ];
-            if (poly_s) poly_s[r] = v[3 * r + R_POLY_SIGNED];
-            if (poly_a) poly_a[r] = v[3 * r + R_POLY_ABS];
+            const double *x = &v[(size_t)r * kResultSlots];
+            if (plaq) plaq[r] = x[R_PLAQ];
+            if (poly_s) poly_s[r] = x[R_POLY_SIGNED];
+            if (poly_a) poly_a[r] = x[R_POLY_ABS];
         }
         return SU2_OK;
     }
@@ -732,14 +744,13 @@ public:
     int counts(int reset, uint64_t *proposed, uint64_t *accepted)
     {
         HIP_TRY(launch_counts(ens(), reset, stream));
-        std::vector<unsigned long long> v(2 * (size_t)n);
-        for (int r = 0; r < n; ++r)
-            HIP_TRY_DRAIN(hipMemcpyAsync(&v[2 * r], results(r) + R_COUNTS, 2 * sizeof(uint64_t),
-                                         hipMemcpyDeviceToHost, stream), stream);
-        HIP_TRY(hipStreamSynchronize(stream));
+        std::vector<double> v;
+        if (int rc = read_results(v)) return rc;
         for (int r = 0; r < n; ++r) {
-            if (proposed) proposed[r] = v[2 * r];
-            if (accepted) accepted[r] = v[2 * r + 1];
+            uint64_t c[2];  // the counts' bits
+            std::memcpy(c, &v[(size_t)r * kResultSlots + R_COUNTS], sizeof(c));
+            if (proposed) proposed[r] = c[0];
+            if (accepted) accepted[r] = c[1];
         }
         return SU2_OK;
     }

@@ -22,15 +22,16 @@ struct Lat3 {
     Geom g;
     float4 *links;
     unsigned long long *acc;  // kNumAcc x kBuckets fixed-point accumulators
-    double *results;          // kRes3 result slots
-    double *hist;             // kHist3 plaquette history rows
+    double *results;          // kRes3 result slots per replica, back to back
+    double *hist;             // plaquette history rows of nrep values (kHist3 rows)
     uint32_t *ctr;            // device counters: [0] sweep index, [1] history row of captured sweeps
     float beta;
     uint32_t replica;
     // Batches of replicas with the extents of g: every launch has grid z =
     // nrep, and replica r = blockIdx.z uses links + r * link_stride (float4),
-    // the acc, results, hist and ctr of its own scratch (r * scratch_stride
-    // bytes on), coupling betas[r] (device array; nullptr: beta) and Philox
+    // the acc and ctr of its own scratch (r * scratch_stride bytes on), its
+    // entries of results and hist (side by side, so that the host reads them
+    // in one copy), coupling betas[r] (device array; nullptr: beta) and Philox
     // replica id replica + r.  A single lattice is a batch of one.
     const float *betas;
     size_t link_stride;

@@ -39,8 +39,8 @@ __device__ __forceinline__ Lat3 rep3(const Lat3 &L0)
     const size_t off = (size_t)r * L0.scratch_stride;
     L.links = L0.links + (size_t)r * L0.link_stride;
     L.acc = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(L0.acc) + off);
-    L.results = reinterpret_cast<double *>(reinterpret_cast<char *>(L0.results) + off);
-    L.hist = reinterpret_cast<double *>(reinterpret_cast<char *>(L0.hist) + off);
+    L.results = L0.results + (size_t)r * kRes3;
+    L.hist = L0.hist + r;
     L.ctr = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(L0.ctr) + off);
     if (L0.betas) L.beta = L0.betas[r];
     L.replica = L0.replica + r;
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(kBuckets) void su3_finish_kernel(Lat3 L0, int flags
             if (flags & 4) {
                 // flags 16: the row comes from the device row counter (captured sweeps)
                 const uint32_t r = (flags & 16) ? L.ctr[1]++ : (uint32_t)row;
-                L.hist[r] = p;
+                L.hist[(size_t)r * L.nrep] = p;
             }
         }
     }

@@ -64,9 +64,10 @@ struct su3_batch : su3_ctx {};
 
 namespace {
 
-constexpr size_t kScratch3 = kAccBytes + (size_t)kRes3 * 8 + (size_t)kHist3 * 8 + 256;
-// scratch of one replica (accumulators, results, history, counters)
-constexpr size_t kStride3 = (kScratch3 + 255) & ~(size_t)255;
+// Scratch of one replica (accumulators, counters); after the replicas' come
+// their results and the history rows.
+constexpr size_t kStride3 = (kAccBytes + 256 + 255) & ~(size_t)255;
+constexpr size_t kShared3 = ((size_t)kRes3 + (size_t)kHist3) * sizeof(double);  // per replica
 
 int64_t volume3(const int32_t *d) { return (int64_t)d[0] * d[1] * d[2] * d[3]; }
 
@@ -122,11 +123,21 @@ int lg_tile(int tile, uint32_t cur, uint32_t *out)
 // (host[r * nres + i]).
 int finish_to_host(su3_ctx *c, int flags, int first, int nres, double *host)
 {
+    const size_t nr = (size_t)c->nrep, w = sizeof(double) * (size_t)nres;
     HIP_TRY(launch_su3_finish(c->L, flags, 0, c->stream));
-    HIP_TRY(hipMemcpy2DAsync(host, sizeof(double) * (size_t)nres, c->L.results + first, kStride3,
-                             sizeof(double) * (size_t)nres, (size_t)c->nrep,
-                             hipMemcpyDeviceToHost, c->stream));
+    if (nr == 1) {
+        HIP_TRY(hipMemcpyAsync(host, c->L.results + first, w, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return SU2_OK;
+    }
+    // every replica's slots in one copy (a strided one runs row by row)
+    std::unique_ptr<double[]> all(new (std::nothrow) double[nr * kRes3]);
+    if (!all) return fail(SU2_ENOMEM, "host staging of the results");
+    HIP_TRY(hipMemcpyAsync(all.get(), c->L.results, sizeof(double) * nr * kRes3,
+                           hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    for (size_t r = 0; r < nr; ++r)
+        for (int i = 0; i < nres; ++i) host[r * (size_t)nres + i] = all[r * kRes3 + first + i];
     return SU2_OK;
 }
 
@@ -196,25 +207,27 @@ int init3(su3_ctx *c, int32_t n, const int32_t dims[4], const double *betas, dou
     c->L.scratch_stride = kStride3;
     const size_t beta_bytes = betas ? sizeof(float) * (size_t)n : 0;
     hipError_t e = hipMalloc(&c->links_mem, su3_links_bytes(dims) * (size_t)n);
-    if (e == hipSuccess) e = hipMalloc(&c->scratch_mem, kStride3 * (size_t)n + beta_bytes);
-    if (e == hipSuccess) e = hipMemsetAsync(c->scratch_mem, 0, kStride3 * (size_t)n, c->stream);
+    const size_t scratch = (kStride3 + kShared3) * (size_t)n;
+    if (e == hipSuccess) e = hipMalloc(&c->scratch_mem, scratch + beta_bytes);
+    if (e == hipSuccess) e = hipMemsetAsync(c->scratch_mem, 0, scratch, c->stream);
     std::unique_ptr<float[]> bf;
     if (e == hipSuccess && betas) {
         bf.reset(new (std::nothrow) float[(size_t)n]);
         if (!bf) return fail(SU2_ENOMEM, "host staging of the couplings");
         for (int32_t r = 0; r < n; ++r) bf[r] = (float)betas[r];
         float *bd = reinterpret_cast<float *>(static_cast<unsigned char *>(c->scratch_mem) +
-                                              kStride3 * (size_t)n);
+                                              scratch);
         e = hipMemcpyAsync(bd, bf.get(), beta_bytes, hipMemcpyHostToDevice, c->stream);
         c->L.betas = bd;
     }
     if (e == hipSuccess) {
         c->L.links = static_cast<float4 *>(c->links_mem);
         c->L.acc = static_cast<unsigned long long *>(c->scratch_mem);
+        c->L.ctr = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(c->scratch_mem) +
+                                                kAccBytes);  // zeroed above
         c->L.results = reinterpret_cast<double *>(static_cast<unsigned char *>(c->scratch_mem) +
-                                                  kAccBytes);
-        c->L.hist = c->L.results + kRes3;
-        c->L.ctr = reinterpret_cast<uint32_t *>(c->L.hist + kHist3);  // zeroed above
+                                                  kStride3 * (size_t)n);
+        c->L.hist = c->L.results + (size_t)kRes3 * (size_t)n;
         e = launch_su3_init(c->L, start, seed, c->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);  // bf outlives its copy
@@ -309,11 +322,6 @@ int heatbath3(su3_ctx *c, int32_t nsweeps, int32_t reunit_every, double *plaq_hi
     if (nsweeps < 0 || reunit_every < 0)
         return fail(SU2_EINVAL, "nsweeps and reunit_every must be >= 0");
     const size_t nr = (size_t)c->nrep;
-    std::unique_ptr<double[]> stage;
-    if (plaq_hist && nr > 1) {
-        stage.reset(new (std::nothrow) double[nr * (size_t)std::min<int32_t>(nsweeps, kHist3)]);
-        if (!stage) return fail(SU2_ENOMEM, "host staging of the plaquette history");
-    }
     int32_t done = 0;
     while (done < nsweeps) {
         const int32_t chunk = plaq_hist ? std::min<int32_t>(nsweeps - done, kHist3)
@@ -324,19 +332,11 @@ int heatbath3(su3_ctx *c, int32_t nsweeps, int32_t reunit_every, double *plaq_hi
                 return rc;
             ++c->sweep;
         }
-        if (plaq_hist && nr == 1) {
-            HIP_TRY(hipMemcpyAsync(plaq_hist + done, c->L.hist, sizeof(double) * (size_t)chunk,
-                                   hipMemcpyDeviceToHost, c->stream));
+        if (plaq_hist) {  // rows of nr values, as the host holds them
+            HIP_TRY(hipMemcpyAsync(plaq_hist + (size_t)done * nr, c->L.hist,
+                                   sizeof(double) * (size_t)chunk * nr, hipMemcpyDeviceToHost,
+                                   c->stream));
             HIP_TRY(hipStreamSynchronize(c->stream));
-        } else if (plaq_hist) {
-            // replica r's rows sit in its own scratch: [r][j] staged, then [j][r]
-            const size_t w = sizeof(double) * (size_t)chunk;
-            HIP_TRY(hipMemcpy2DAsync(stage.get(), w, c->L.hist, kStride3, w, nr,
-                                     hipMemcpyDeviceToHost, c->stream));
-            HIP_TRY(hipStreamSynchronize(c->stream));
-            for (size_t r = 0; r < nr; ++r)
-                for (int32_t j = 0; j < chunk; ++j)
-                    plaq_hist[(size_t)(done + j) * nr + r] = stage[r * (size_t)chunk + (size_t)j];
         }
         done += chunk;
     }
