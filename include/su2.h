@@ -218,7 +218,9 @@ int su2_synchronize(su2_ctx *ctx);
  * 0 = as many as the device holds at once), bits 4-5 = log2 of the items it
  * takes per ticket, bit 6 = batches: all pass workgroups of a replica on one
  * XCD (replicas spread over the XCDs by size, each replica's blocks in
- * order on its XCD's L2; bit 0 is then unused), bit 7 = single FP32 lattices:
+ * order on its XCD's L2; bit 0 is then unused; a batch whose launch was never
+ * set runs so by itself where its replicas are small enough for the L2s and
+ * fill the XCDs evenly), bit 7 = single FP32 lattices:
  * the pass with its neighbour links staged in LDS (heat bath and
  * over-relaxation; SU2_LEARNED keeps the plain pass): workgroups of R =
  * tile_z full x-rows of an (x, y) plane walk T = tile_t planes along t

@@ -249,7 +249,13 @@ __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
     // LEARNED: the spline table in LDS (filled once per workgroup)
     __shared__ float4 stab4[LEARNED ? 1 + kNNRows * kNNRow / 4 : 1];
     const float *ltab = LEARNED ? load_table_lds(stab4, table) : nullptr;
-    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+    for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
+        // A reversed pass over a batch takes the replicas, too, in reverse order
+        // (the workgroup ids in groups of 8, which keeps each on its XCD), and so
+        // starts on what the pass before left in the caches: 39 x 32^3 x Nt
+        // 790 -> 738 us per sweep, 32 x 16^4 234 -> 223 us
+        const bool flip = reverse && bmap && (total & 7u) == 0u;
+        const uint32_t b = flip ? total - 8u - (i & ~7u) + (i & 7u) : i;
         uint32_t r, local;
         if (amap) {
             const uint2 a = amap[b];
@@ -264,8 +270,9 @@ __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
         if (local >= R.nblocks) continue;  // padding workgroup (uniform)
         const Geom &g = R.g;
         // the blocks of an XCD-affine replica run in order on one XCD
-        const uint32_t blk = amap ? (reverse ? R.nblocks - 1u - local : local)
-                                  : logical_block(local, R.nblocks, remap, reverse);
+        const int rev = reverse && !flip;
+        const uint32_t blk = amap ? (rev ? R.nblocks - 1u - local : local)
+                                  : logical_block(local, R.nblocks, remap, rev);
         const uint32_t gid = blk * blockDim.x + threadIdx.x;
         float meas = 0.0f;
         int acc = -1;
