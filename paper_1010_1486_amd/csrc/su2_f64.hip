@@ -189,13 +189,11 @@ __global__ void init64_kernel(const Rep *__restrict__ reps, int hot, uint32_t k0
 // per link, in the traversal and workgroup order of the FP32 pass.  MEASURE:
 // (1/2)Tr(U'_MU V_nu) summed over nu < MU into the plaquette accumulator.
 template <int MU, bool MEASURE>
-__global__ __launch_bounds__(256) void pass64_kernel(const Rep *__restrict__ reps, int par,
-                                                     uint32_t k0, uint32_t k1, int remap,
-                                                     int reverse)
+__global__ __launch_bounds__(256) void pass64_kernel(Rep R, int par, uint32_t k0, uint32_t k1,
+                                                     int remap, int reverse)
 {
-    const Rep &R = reps[0];
     const Geom &g = R.g;
-    const uint32_t blk = logical_block(blockIdx.x, R.nblocks, remap, reverse);
+    const uint32_t blk = logical_block(blockIdx.x, gridDim.x, remap, reverse);
     const uint32_t gid = blk * blockDim.x + threadIdx.x;
     double meas = 0.0;
     if (gid < g.vh) {
@@ -251,55 +249,75 @@ __device__ __forceinline__ double site_plaquettes64(const Geom &g, const double 
     const int opp = par ^ 1;
     const PassSite s = pass_site(g, gid, par);
     const Deltas d = neighbour_deltas(g, s);
-    QD U[4];
+    // all 32 loads of the sixteen links as one group ahead of the products
+    QD U[4], F[4][4];
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) U[mu] = ldd(links, g.vh, mu, par, s.h);
+    for (int mu = 0; mu < 4; ++mu) {
+        U[mu] = ldd(links, g.vh, mu, par, s.h);
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu)
+            if (nu != mu) F[mu][nu] = ldd(links, g.vh, nu, opp, s.h + d.p[mu]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     double acc = 0.0;
 #pragma unroll
     for (int mu = 0; mu < 4; ++mu)
 #pragma unroll
         for (int nu = mu + 1; nu < 4; ++nu) {
-            const QD P = dmul(U[mu], ldd(links, g.vh, nu, opp, s.h + d.p[mu]));
-            const QD Qq = dmul(U[nu], ldd(links, g.vh, mu, opp, s.h + d.p[nu]));
+            const QD P = dmul(U[mu], F[mu][nu]);
+            const QD Qq = dmul(U[nu], F[nu][mu]);
             acc += ddot(P, Qq);  // (1/2) Tr(P Q^+)
         }
     return acc;
 }
 
-// One thread per half-site: the plaquettes rooted at both of its sites (the
-// two parities), so that each link class is read as own and as neighbour
-// links by the same workgroup.
-__global__ __launch_bounds__(256) void plaquette64_kernel(const Rep *__restrict__ reps)
+// One thread per site: a workgroup takes both parities of 256 half-sites.  (One
+// thread for both sites of a half-site: 18.0 us at 24^4.)
+__global__ __launch_bounds__(512) void plaquette64_kernel(const Rep *__restrict__ reps)
 {
     const Rep &R = reps[0];
     const Geom &g = R.g;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t i = blockIdx.x * 256u + (threadIdx.x & 255u);
     double acc = 0.0;
-    if (i < g.vh) {
-        const double *links = reinterpret_cast<const double *>(R.links);
-        acc = site_plaquettes64(g, links, i, 0) + site_plaquettes64(g, links, i, 1);
-    }
+    if (i < g.vh)
+        acc = site_plaquettes64(g, reinterpret_cast<const double *>(R.links), i,
+                                threadIdx.x >= 256u ? 1 : 0);
     block_accumulate(acc, R.acc, ACC_PLAQ, blockIdx.x);
 }
 
-// One thread per spatial site: L(x) = (1/2)Tr prod_t U_3(x, t), t = 0 leftmost.
-__global__ __launch_bounds__(256) void polyakov64_kernel(const Rep *__restrict__ reps)
+// L(x) = (1/2)Tr prod_t U_3(x, t), t = 0 leftmost.  A workgroup holds 256
+// spatial sites and S groups of 256 threads; group w multiplies the w-th of S
+// t-segments, group 0 the segment products.  (One thread per site, its Nt loads
+// one behind the other: 15.1 us at 24^4.)
+template <int S>
+__global__ __launch_bounds__(256 * S) void polyakov64_kernel(const Rep *__restrict__ reps)
 {
+    __shared__ QD seg[S][256];
     const Rep &R = reps[0];
     const Geom &g = R.g;
     const uint32_t ns3 = (uint32_t)g.nx * g.ny * g.nz;
-    const uint32_t xs = blockIdx.x * blockDim.x + threadIdx.x;
-    double acc = 0.0;
+    const int lane = threadIdx.x & 255, w = threadIdx.x >> 8;
+    const uint32_t xs = blockIdx.x * 256u + (uint32_t)lane;
+    QD P{1.0, 0.0, 0.0, 0.0};
     if (xs < ns3) {
         const double *links = reinterpret_cast<const double *>(R.links);
         const uint32_t x = xs % (uint32_t)g.nx, q = xs / (uint32_t)g.nx;
         const uint32_t y = q % (uint32_t)g.ny, z = q / (uint32_t)g.ny;
         const uint32_t pbase = (x + y + z) & 1u;
-        QD P{1.0, 0.0, 0.0, 0.0};
-        for (int t = 0; t < g.nt; ++t)
+        const int len = g.nt / S;
+#pragma unroll 4
+        for (int t = w * len; t < (w + 1) * len; ++t)
             P = dmul(P, ldd(links, g.vh, 3, (int)((pbase + (uint32_t)t) & 1u),
                             (xs >> 1) + (uint32_t)t * (ns3 >> 1)));
-        acc = P.w;
+    }
+    seg[w][lane] = P;
+    __syncthreads();
+    double acc = 0.0;
+    if (w == 0 && xs < ns3) {
+        QD T = seg[0][lane];
+#pragma unroll
+        for (int k = 1; k < S; ++k) T = dmul(T, seg[k][lane]);
+        acc = T.w;
     }
     block_accumulate(acc, R.acc, ACC_POLY, blockIdx.x);
 }
@@ -325,14 +343,16 @@ template <int MU>
 void pass64_mu(const Ens &e, int par, uint64_t seed, bool measure, const LaunchCfg &cfg,
                hipStream_t stream)
 {
-    const unsigned grid = e.total_blocks;
+    // (sums are rounded per workgroup of pass_block)
+    const int block = cfg.small_block && !measure ? cfg.small_block : cfg.pass_block;
+    const unsigned grid = nblk(e.max_vh, block);
     const int rev = cfg.snake ? par : 0;
     if (measure)
-        hipLaunchKernelGGL((pass64_kernel<MU, true>), dim3(grid), dim3(cfg.pass_block), 0, stream,
-                           e.reps, par, lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev);
+        hipLaunchKernelGGL((pass64_kernel<MU, true>), dim3(grid), dim3(block), 0, stream,
+                           *e.rep0, par, lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev);
     else
-        hipLaunchKernelGGL((pass64_kernel<MU, false>), dim3(grid), dim3(cfg.pass_block), 0, stream,
-                           e.reps, par, lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev);
+        hipLaunchKernelGGL((pass64_kernel<MU, false>), dim3(grid), dim3(block), 0, stream,
+                           *e.rep0, par, lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev);
 }
 
 }  // namespace
@@ -358,15 +378,18 @@ hipError_t launch_pass64(const Ens &e, int mu, int par, uint64_t seed, bool meas
 
 hipError_t launch_plaquette64(const Ens &e, hipStream_t stream)
 {
-    hipLaunchKernelGGL(plaquette64_kernel, dim3(nblk(e.max_vh, 256)), dim3(256), 0, stream,
+    hipLaunchKernelGGL(plaquette64_kernel, dim3(nblk(e.max_vh, 256)), dim3(512), 0, stream,
                        e.reps);
     return hipGetLastError();
 }
 
 hipError_t launch_polyakov64(const Ens &e, hipStream_t stream)
 {
-    hipLaunchKernelGGL(polyakov64_kernel, dim3(nblk(e.max_ns3, 256)), dim3(256), 0, stream,
-                       e.reps);
+    const dim3 grid(nblk(e.max_ns3, 256));
+    if (e.poly_s >= 4)
+        hipLaunchKernelGGL(polyakov64_kernel<4>, grid, dim3(1024), 0, stream, e.reps);
+    else  // even Nt
+        hipLaunchKernelGGL(polyakov64_kernel<2>, grid, dim3(512), 0, stream, e.reps);
     return hipGetLastError();
 }
 

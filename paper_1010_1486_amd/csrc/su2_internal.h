@@ -81,6 +81,8 @@ constexpr size_t kRepScratch = sizeof(Counters) + kAccBytes + kResultSlots * siz
 
 struct LaunchCfg {
     int pass_block = 256;
+    int small_block = 0;      // > 0: workgroup size of a single lattice's passes that
+                              // measure nothing, see small_block_for
     bool xcd_remap = true;
     bool snake = true;        // odd-parity passes traverse backwards
     uint32_t grid_cap = 0;    // > 0: persistent pass grid of at most this many workgroups
@@ -91,6 +93,16 @@ struct LaunchCfg {
     uint32_t march_R = 0;     // > 0: single lattices run the LDS-staged march pass
     uint32_t march_T = 0;     //      (tiles of march_R rows, march_T planes per workgroup)
 };
+
+// Pass workgroups of one wave for single lattices whose launch was not set and
+// whose waves do not fill the chip several times over: they spread over more
+// CUs.  us per pass, 256 / 64 threads: FP32 8^4 4.03 / 3.74, 16^4 4.41 / 4.11,
+// 20^4 4.97 / 4.81, 24^4 5.80 / 5.88; FP64 16^4 7.89 / 7.17, 24^4 12.84 / 12.63,
+// 32^4 27.4 / 26.5, 48^4 138.4 / 137.4.  Returns 0 for pass_block.
+inline int small_block_for(uint32_t vh, bool f64)
+{
+    return vh <= (f64 ? 1u << 19 : 1u << 17) ? 64 : 0;
+}
 
 // ------------------------------------------------------------- work queue
 // A persistent launch runs ns sweeps of every replica.  Each replica belongs
@@ -203,6 +215,10 @@ struct Ens {
     uint32_t max_ns3;         // largest spatial volume
     int poly_s;               // Polyakov segments (common divisor of every Nt)
     uint32_t plane_hs = 0;    // half-sites per (x, y) plane if every replica has the same, else 0
+    // a single lattice's descriptor on the host (nullptr for a batch): its pass
+    // kernels take it as an argument, one dependent load less before the first
+    // neighbour address
+    const Rep *rep0 = nullptr;
 };
 
 // Kernel launchers (all asynchronous on `stream`; return hipError_t).

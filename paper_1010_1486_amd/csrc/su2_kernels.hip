@@ -238,6 +238,30 @@ __device__ __forceinline__ const float *load_table_lds(float4 *stab4, const floa
 // plaquette of the end-of-sweep configuration exactly once.  With NORM every
 // stored link is reunitarised first (the last pass stage of a
 // reunitarisation sweep when the reunitarisation is fused into the passes).
+// The pass of a single lattice (heat bath or over-relaxation): its descriptor
+// is a kernel argument, so the first neighbour address waits for one load
+// less (us per pass, loaded / argument: 8^4 4.35 / 4.03, 16^4 4.74 / 4.41, 32^4
+// 13.2 / 12.3); sums and links are pass_kernel's.
+template <int MU, bool MEASURE, bool OR, bool NORM>
+__global__ __launch_bounds__(256) void single_pass_kernel(Rep R, uint32_t total, int par,
+                                                          uint32_t k0, uint32_t k1, int remap,
+                                                          int reverse)
+{
+    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
+        const uint32_t gid = logical_block(b, total, remap, reverse) * blockDim.x + threadIdx.x;
+        float meas = 0.0f;
+        int acc = -1;
+        if (gid < R.g.vh) {
+            // uniform: a scalar load through the constant address space
+            const uint32_t sweep =
+                *(const __attribute__((address_space(4))) uint32_t *)&R.cnt->sweep;
+            update_site<MU, MEASURE, false, OR, NORM>(R, gid, par, sweep, k0, k1, nullptr, meas,
+                                                      acc);
+        }
+        if (MEASURE) block_accumulate((double)meas, R.acc, ACC_PLAQ, b);
+    }
+}
+
 template <int MU, bool MEASURE, bool LEARNED, bool OR = false, bool NORM = false>
 __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
                                                    const uint32_t *__restrict__ bmap,
@@ -507,10 +531,36 @@ __global__ __launch_bounds__(kBuckets) void sweep_end_kernel(const Rep *__restri
                                                              int nrep, int flags,
                                                              double *__restrict__ hist)
 {
+    // the sums that were measured (the others are zero), both loaded and
+    // reduced together
+    __shared__ unsigned long long part[2][kBuckets / 64];
     const Rep &R = reps[blockIdx.z];
-    const unsigned long long tp = take_total(R.acc, ACC_PLAQ);
-    const unsigned long long tl = take_total(R.acc, ACC_POLY);
+    unsigned long long v[2] = {0ull, 0ull};
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+        if (flags & (1 << a)) v[a] = *bucket(R.acc, ACC_PLAQ + a, threadIdx.x);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+        if (flags & (1 << a)) *bucket(R.acc, ACC_PLAQ + a, threadIdx.x) = 0ull;
+    if (flags & 3) {  // uniform
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            v[0] += __shfl_down(v[0], off, 64);
+            v[1] += __shfl_down(v[1], off, 64);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            part[0][threadIdx.x >> 6] = v[0];
+            part[1][threadIdx.x >> 6] = v[1];
+        }
+        __syncthreads();
+    }
     if (threadIdx.x == 0) {
+        unsigned long long tp = 0ull, tl = 0ull;
+        if (flags & 3)
+            for (int i = 0; i < kBuckets / 64; ++i) {
+                tp += part[0][i];
+                tl += part[1][i];
+            }
         Counters *c = R.cnt;
         const Geom &g = R.g;
         if ((flags & 4) && hist) {
@@ -1542,18 +1592,35 @@ template <int MU, bool LEARNED, bool OR, bool NORM>
 void launch_pass_mn(const Ens &e, int par, uint64_t seed, bool measure, const float *table,
                     const LaunchCfg &cfg, hipStream_t stream)
 {
-    const unsigned total = e.amap ? e.amap_len : e.total_blocks;
+    // small workgroups where no sum (rounded per workgroup) and no spline table
+    // (loaded per workgroup) depends on them
+    const bool small = !LEARNED && !measure && e.rep0 && cfg.small_block;
+    const int block = small ? cfg.small_block : cfg.pass_block;
+    const unsigned total =
+        e.amap ? e.amap_len : small ? nblk(e.max_vh, block) : e.total_blocks;
     unsigned grid = total;
     if (cfg.grid_cap && cfg.grid_cap < grid) grid = cfg.grid_cap & ~7u;
     if (grid == 0) grid = 8;
     const int rev = cfg.snake ? par : 0;
+    if constexpr (!LEARNED)
+        if (e.rep0) {
+            if (measure)
+                hipLaunchKernelGGL((single_pass_kernel<MU, true, OR, NORM>), dim3(grid),
+                                   dim3(block), 0, stream, *e.rep0, total, par, lo32(seed),
+                                   hi32(seed), (int)cfg.xcd_remap, rev);
+            else
+                hipLaunchKernelGGL((single_pass_kernel<MU, false, OR, NORM>), dim3(grid),
+                                   dim3(block), 0, stream, *e.rep0, total, par, lo32(seed),
+                                   hi32(seed), (int)cfg.xcd_remap, rev);
+            return;
+        }
     if (measure)
         hipLaunchKernelGGL((pass_kernel<MU, true, LEARNED, OR, NORM>), dim3(grid),
-                           dim3(cfg.pass_block), 0, stream, e.reps, e.bmap, e.amap, total, par,
+                           dim3(block), 0, stream, e.reps, e.bmap, e.amap, total, par,
                            lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev, table);
     else
         hipLaunchKernelGGL((pass_kernel<MU, false, LEARNED, OR, NORM>), dim3(grid),
-                           dim3(cfg.pass_block), 0, stream, e.reps, e.bmap, e.amap, total, par,
+                           dim3(block), 0, stream, e.reps, e.bmap, e.amap, total, par,
                            lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev, table);
 }
 

@@ -293,6 +293,7 @@ public:
     double *wilson_work = nullptr;  // partial sums of the Wilson loops (device, owned)
     uint2 *amap = nullptr;  // XCD-affine pass map (device, owned), see Ens
     uint32_t amap_len = 0;
+    Rep rep0{};  // the first replica's descriptor, as uploaded
     LaunchCfg cfg;
     // No launch configuration was set: batches of replicas with fields up to
     // three times an XCD's 4 MB L2 run XCD-affine.  Measured per sweep, plain
@@ -372,7 +373,7 @@ public:
     Ens ens() const
     {
         return Ens{d_reps(), d_bmap(), amap, amap_len, n,
-                   total_blocks, max_vh, max_ns3, poly_s, plane_hs};
+                   total_blocks, max_vh, max_ns3, poly_s, plane_hs, n == 1 ? &rep0 : nullptr};
     }
 
     void drop_graph()
@@ -391,6 +392,9 @@ public:
     {
         drop_graph();
         geom.resize(n);
+        cfg.small_block = auto_launch && n == 1
+                              ? small_block_for((uint32_t)(volume_of(dims[0].data()) / 2), f64)
+                              : 0;
         total_blocks = slot_layout(dims, cfg.pass_block, first_block, nblocks);
         max_vh = max_ns3 = 0;
         poly_s = 8;
@@ -483,6 +487,7 @@ public:
         }
         HIP_TRY(hipStreamSynchronize(stream));
         HIP_TRY(hipMemcpy(d_reps(), h.data(), n * sizeof(Rep), hipMemcpyHostToDevice));
+        rep0 = h[0];
         if (n > 1) {
             std::vector<uint32_t> map(total_blocks);
             for (int r = 0; r < n; ++r) {

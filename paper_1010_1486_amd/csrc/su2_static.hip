@@ -84,8 +84,9 @@ int sweep_measure_static(float *links, const int32_t dims[4], double beta, uint6
     if (ns == 0) return SU2_OK;
 
     // the descriptor a context of these extents holds in its default launch
-    const LaunchCfg cfg;
+    LaunchCfg cfg;
     const Geom g = make_geom(dims, 3, 3);
+    cfg.small_block = small_block_for(g.vh, false);
     if (!geom_selfcheck(g))
         return fail(SU2_ERANGE, "index arithmetic self-check failed for these extents");
     Rep *reps = reinterpret_cast<Rep *>(ptr);
@@ -106,7 +107,7 @@ int sweep_measure_static(float *links, const int32_t dims[4], double beta, uint6
     int poly_s = 8;
     while (dims[3] % poly_s) poly_s /= 2;
     const Ens e{reps, nullptr, nullptr, 0u, 1, r.nblocks, g.vh,
-                (uint32_t)(dims[0] * dims[1] * dims[2]), poly_s, g.P};
+                (uint32_t)(dims[0] * dims[1] * dims[2]), poly_s, g.P, &r};
 
     hipLaunchKernelGGL(put_rep_kernel, dim3(1), dim3(1), 0, stream, r, reps);
     STATIC_TRY(hipGetLastError());

@@ -649,7 +649,7 @@ void launch_pass_mu(const Lat3 &L, int par, uint32_t k0, uint32_t k1,
     // fill the XCDs evenly: each replica's workgroups on one XCD.  Per sweep,
     // with the replicas split over the XCDs and in forward order before: 64 x
     // 16^3 x 4 (3.1 MB) 442 -> 336 us, 64 x 8^4 142 -> 117, 16 x 12^4 161 -> 143,
-    // 16 x 16^4 (12.6 MB, in plain but reversed order) 366 -> 338.
+    // 16 x 16^4 (12.6 MB) 366 -> 338.
     const uint32_t nz8 = (L.nrep + 7u) & ~7u;
     const int affine = remap && L.nrep > 1 && (uint64_t)L.g.vh * 384u <= (12u << 20) &&
                        10u * nz8 <= 11u * L.nrep && nz8 <= 65535u;
