@@ -210,7 +210,9 @@ int su2_synchronize(su2_ctx *ctx);
  * threads); flags: bit 0 = XCD-contiguous workgroup remap, bit 1 = disable
  * the alternating (forward, backward) pass order, bit 2 = disable the
  * whole-sweep kernel for small lattices (by default, when every V/2 <= 2048,
- * one launch runs whole sweeps with one workgroup per lattice), bit 3 = run
+ * one launch runs whole sweeps with one workgroup per lattice; an unset launch
+ * of a single lattice up to V/2 = 5120 with several workgroups of one XCD, with
+ * the same results), bit 3 = run
  * sweeps as one persistent work-queue launch per call (every pass, the
  * reunitarisation and the measurements of all replicas, ordered per replica
  * by completion counters; each replica is served by one XCD, replicas spread

@@ -49,10 +49,23 @@ __host__ __device__ inline uint32_t *row_counter(Counters *c, bool graph)
 
 // Shared state of the persistent work-queue launch: one queue per XCD.
 constexpr int kMaxQueues = 16;  // the XCC id is 4 bits
+// One lattice's team of workgroups on one XCD (team_sweeps_kernel).  All zero
+// between launches.
+struct TeamState {
+    uint32_t target;  // 1 + XCC id of the first workgroup that came
+    uint32_t join;    // workgroups of that XCD that came; kTeamClosed once the team is closed
+    uint32_t size;    // workgroups of the team, published by its first
+    uint32_t pad0[29];
+    uint32_t bar;     // arrivals at the team's barriers
+    uint32_t pad1[31];
+};
+constexpr uint32_t kTeamClosed = 1u << 31;
+
 struct QueueState {
     uint32_t ticket[kMaxQueues][32];  // next item of queue q (own 128-byte line each)
     uint32_t error;                   // nonzero: a bounded wait ran out or work was left over
     uint32_t pad0[31];
+    TeamState team;
     int32_t rank[kMaxQueues];         // XCC id -> queue (-1: the XCD takes no work)
     uint32_t slots[kMaxQueues];       // items per stage of queue q
     uint32_t off[kMaxQueues];         // first entry of queue q in the slot -> replica map
@@ -200,6 +213,13 @@ constexpr uint32_t kSmallMaxVh = 2048;
 // Largest V/2 whose heat-bath sweeps keep the field in LDS (three threads per
 // link, at most 960, and 208 bytes of LDS per half-site within 64 KiB).
 constexpr uint32_t kTinyMaxVh = 312;
+// V/2 of the lattices whose sweeps a team of workgroups on one XCD runs.  Up to 20
+// tiles of 256 links; with more the barriers cost what the launches did.  From 16
+// on only calls of several sweeps: a lone one at 20 tiles took 47 us, its pass
+// launches 45.  The heat bath alone only past two tiles, up to which one workgroup
+// is the faster (us per sweep, one workgroup / team: V/2 432 20.0 / 21.7, 648
+// 24.5 / 21.4); further figures at team_sweeps_kernel.
+constexpr uint32_t kTeamMaxVh = 5120, kTeamLoneMaxVh = 4096, kTeamHeatbathMinVh = 513;
 
 // Everything a launch needs to address an ensemble on the device.
 struct Ens {
@@ -278,6 +298,15 @@ hipError_t launch_queue_sweeps(const Ens &e, const QueuePlan &plan, const uint32
                                uint64_t seed, int block, uint32_t grid, int grain, bool snake,
                                double *hist, const float *table, QueueState *qs,
                                uint32_t spin_limit, hipStream_t stream);
+// ns sweeps (each the heat bath, then n_or over-relaxation sweeps) of a single
+// FP32 lattice by a team of workgroups on one XCD, followed by a launch that
+// advances the counters and clears the team.  site: sums in per-site fixed
+// point and the reunitarisation as launch_small_sweeps; else per workgroup of
+// 256 links as the pass launches, without reunitarisation.  flags: 1, 2, 4, 8
+// as launch_small_sweeps, 16 the passes alone (no sums, rows or sweep advance).
+hipError_t launch_team_sweeps(const Ens &e, int ns, int n_or, uint64_t seed, int reunit_every,
+                              bool site, int flags, double *hist, QueueState *qs,
+                              uint32_t spin_limit, hipStream_t stream);
 // Bit mask of the XCC ids that run workgroups of a large launch (one-time
 // probe of the current device; synchronous).
 hipError_t probe_xcc_mask(uint32_t *mask);

@@ -612,6 +612,7 @@ __global__ __launch_bounds__(kBuckets) void set_counter_kernel(const Rep *__rest
         if (qs && blockIdx.z == 0) {
             for (int k = 0; k < kMaxQueues; ++k) qs->ticket[k][0] = 0u;
             qs->error = 0u;
+            qs->team.target = qs->team.join = qs->team.size = qs->team.bar = 0u;
         }
     }
     if (which & 4)
@@ -1487,6 +1488,259 @@ __global__ void queue_epilogue_kernel(const Rep *__restrict__ reps, QueuePlan pl
         for (int k = 0; k < kMaxQueues; ++k) qs->ticket[k][0] = 0u;
 }
 
+// ------------------------------------------------------------- XCD team
+// Whole sweeps of one lattice in one launch by the workgroups of one XCD, with
+// a barrier among them after every pass.  The launch brings gridDim / 8
+// workgroups to each XCD; the XCD of the first one takes the lattice, the
+// others leave.  The team is whoever of that XCD came before its first
+// workgroup closed it (when all expected ones were there, or after a bounded
+// wait), so a barrier only ever waits for workgroups that are running, whatever
+// else occupies the GPU; the 256-link tiles are dealt out by rank.  Ordering is
+// queue_wait's: a pass's stores have reached the XCD's L2 (vmcnt 0) before its
+// workgroup arrives, and an agent-scope acquire drops stale L1 lines.  Links and
+// sums are those of the launches it replaces, bit for bit.
+//
+// Bound: per pass the update's own latency and one barrier, which grows with
+// the workgroups (arrivals, and the acquires' L1 invalidations, about 90 ns
+// each).  us per heat-bath sweep, one workgroup or pass launches / team: 6^4
+// 24.5 / 21.4, 8^4 53.6 / 22.6, 10^4 33.9 / 28.9; with both measurements 25.7 /
+// 25.5, 55.1 / 27.3, 42.3 / 36.4; with an over-relaxation sweep 64.7 / 44.0,
+// 65.2 / 44.2, 66.2 / 56.7.  12^4 (41 tiles) with the plaquette 42 / 51.
+__device__ __forceinline__ uint32_t team_load(const uint32_t *p)
+{
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Rank in the team (~0u: not in it) and its size, in every thread.
+__device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t &size)
+{
+    __shared__ uint32_t s_rank, s_size;
+    if (threadIdx.x == 0) {
+        const uint32_t me = xcc_id() + 1u;
+        uint32_t rank = 0xFFFFFFFFu, n = 0u, old = 0u;
+        __hip_atomic_compare_exchange_strong(&ts->target, &old, me, __ATOMIC_RELAXED,
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (old == 0u || old == me) {
+            const uint32_t j = __hip_atomic_fetch_add(&ts->join, 1u, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+            if (!(j & kTeamClosed)) {
+                rank = j;
+                if (j == 0u) {
+                    const uint32_t want = gridDim.x >> 3;
+                    for (int i = 0; i < 64 && team_load(&ts->join) < want; ++i)
+                        __builtin_amdgcn_s_sleep(4);
+                    n = __hip_atomic_fetch_or(&ts->join, kTeamClosed, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&ts->size, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                } else {
+                    while ((n = team_load(&ts->size)) == 0u) __builtin_amdgcn_s_sleep(2);
+                }
+            }
+        }
+        s_rank = rank;
+        s_size = n;
+    }
+    __syncthreads();
+    size = s_size;
+    return s_rank;
+}
+
+// Barrier number `phase` (from 1) of the team; every wait is bounded.
+__device__ __forceinline__ void team_barrier(QueueState *qs, uint32_t size, uint32_t phase,
+                                             uint32_t spin_limit)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t goal = size * phase;
+        __hip_atomic_fetch_add(&qs->team.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t i = 0; team_load(&qs->team.bar) < goal; ++i) {
+            if (i > spin_limit) {
+                __hip_atomic_store(&qs->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+    l1_invalidate();
+}
+
+template <int MU, bool MEASURE, bool OR, bool SITE>
+__device__ __forceinline__ void team_pass(const Rep &R, int par, uint32_t rank, uint32_t size,
+                                          uint32_t sweep, uint32_t k0, uint32_t k1,
+                                          unsigned long long &psum)
+{
+    for (uint32_t tile = rank; tile < R.nblocks; tile += size) {
+        const uint32_t gid = tile * blockDim.x + threadIdx.x;
+        float m = 0.0f;
+        int a = -1;
+        if (gid < R.g.vh)
+            update_site<MU, MEASURE, false, OR>(R, gid, par, sweep, k0, k1, nullptr, m, a);
+        if (MEASURE) {
+            if (SITE) psum += gid < R.g.vh ? to_fixed((double)m) : 0ull;
+            else block_accumulate((double)m, R.acc, ACC_PLAQ, tile);
+        }
+    }
+}
+
+template <int MU, bool OR, bool SITE>
+__device__ __forceinline__ void team_pass_m(const Rep &R, int par, bool measure, uint32_t rank,
+                                            uint32_t size, uint32_t sweep, uint32_t k0,
+                                            uint32_t k1, unsigned long long &psum)
+{
+    if (measure) team_pass<MU, MU != 0, OR, SITE>(R, par, rank, size, sweep, k0, k1, psum);
+    else team_pass<MU, false, OR, SITE>(R, par, rank, size, sweep, k0, k1, psum);
+}
+
+template <bool OR, bool SITE>
+__device__ __forceinline__ void team_pass_any(const Rep &R, int mu, int par, bool measure,
+                                              uint32_t rank, uint32_t size, uint32_t sweep,
+                                              uint32_t k0, uint32_t k1, unsigned long long &psum)
+{
+    switch (mu) {
+    case 0: team_pass_m<0, OR, SITE>(R, par, measure, rank, size, sweep, k0, k1, psum); break;
+    case 1: team_pass_m<1, OR, SITE>(R, par, measure, rank, size, sweep, k0, k1, psum); break;
+    case 2: team_pass_m<2, OR, SITE>(R, par, measure, rank, size, sweep, k0, k1, psum); break;
+    default: team_pass_m<3, OR, SITE>(R, par, measure, rank, size, sweep, k0, k1, psum);
+    }
+}
+
+// Per-thread fixed-point values into the accumulator, one add per wave.
+__device__ __forceinline__ void team_add(const Rep &R, int which, uint32_t rank,
+                                         unsigned long long v)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if ((threadIdx.x & 63) == 0)
+        atomicAdd(bucket(R.acc, which, rank * 4u + (threadIdx.x >> 6)), v);
+}
+
+// The team's share of the Polyakov loop.  SITE: sequential products per spatial
+// site; else polyakov_kernel's 64 sites and e.poly_s segments per workgroup.
+template <bool SITE>
+__device__ __forceinline__ void team_polyakov(const Rep &R, int segs, uint32_t rank, uint32_t size)
+{
+    const Geom &g = R.g;
+    const uint32_t ns3 = (uint32_t)g.nx * g.ny * g.nz;
+    auto line = [&](uint32_t xs, int t0, int t1) {
+        const uint32_t x = xs % (uint32_t)g.nx, r = xs / (uint32_t)g.nx;
+        const uint32_t y = r % (uint32_t)g.ny, z = r / (uint32_t)g.ny;
+        const uint32_t pbase = (x + y + z) & 1u;
+        Q P{1.0f, 0.0f, 0.0f, 0.0f};
+        for (int t = t0; t < t1; ++t)
+            P = qmul(P, ldq(R.links, g.vh, 3, (int)((pbase + (uint32_t)t) & 1u),
+                            (xs >> 1) + (uint32_t)t * (ns3 >> 1)));
+        return P;
+    };
+    if constexpr (SITE) {
+        unsigned long long lsum = 0ull;
+        for (uint32_t xs = rank * blockDim.x + threadIdx.x; xs < ns3; xs += size * blockDim.x)
+            lsum += to_fixed((double)line(xs, 0, g.nt).w);
+        team_add(R, ACC_POLY, rank, lsum);
+    } else {
+        __shared__ Q seg[8][64];
+        const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+        const int len = g.nt / segs;
+        for (uint32_t tile = rank; tile * 64u < ns3; tile += size) {
+            const uint32_t xs = tile * 64u + (uint32_t)lane;
+            for (int k = w; k < segs; k += 4)
+                seg[k][lane] = xs < ns3 ? line(xs, k * len, (k + 1) * len)
+                                        : Q{1.0f, 0.0f, 0.0f, 0.0f};
+            __syncthreads();
+            double acc = 0.0;
+            if (w == 0 && xs < ns3) {
+                Q T = seg[0][lane];
+                for (int k = 1; k < segs; ++k) T = qmul(T, seg[k][lane]);
+                acc = (double)T.w;
+            }
+            block_accumulate(acc, R.acc, ACC_POLY, tile);  // ends with a barrier
+        }
+    }
+}
+
+template <bool SITE>
+__global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_or, int segs,
+                                                          uint32_t k0, uint32_t k1,
+                                                          int reunit_every, int flags,
+                                                          double *__restrict__ hist,
+                                                          QueueState *qs, uint32_t spin_limit)
+{
+    uint32_t size;
+    const uint32_t rank = team_join(&qs->team, size);
+    if (rank == 0xFFFFFFFFu) return;
+    const Geom &g = R.g;
+    const uint32_t sweep0 = R.cnt->sweep, row0 = *row_counter(R.cnt, (flags & 8) != 0);
+    const bool want_p = (flags & 1) != 0, want_l = (flags & 2) != 0;
+    const bool rows = (flags & 4) != 0 && hist != nullptr;
+    uint32_t phase = 0u;
+    for (int i = 0; i < ns; ++i) {
+        const uint32_t sweep = sweep0 + (uint32_t)i;
+        const bool reunit =
+            SITE && reunit_every > 0 && ((sweep + 1u) % (uint32_t)reunit_every) == 0u;
+        unsigned long long psum = 0ull;
+        for (int step = 0; step <= n_or; ++step) {
+            const bool fused = want_p && !reunit && step == n_or;
+            for (int p = 0; p < 8; ++p) {
+                const int mu = p >> 1, par = p & 1;
+                const bool measure = fused && par == 1 && mu >= 1;
+                if (step == 0)
+                    team_pass_any<false, SITE>(R, mu, par, measure, rank, size, sweep, k0, k1, psum);
+                else if constexpr (!SITE)
+                    team_pass_any<true, SITE>(R, mu, par, measure, rank, size, sweep, k0, k1, psum);
+                team_barrier(qs, size, ++phase, spin_limit);
+            }
+        }
+        if (reunit) {
+            for (uint32_t j = rank * blockDim.x + threadIdx.x; j < 8u * g.vh;
+                 j += size * blockDim.x) {
+                const uint32_t grp = j / g.vh;
+                reunit_link(R, (int)(grp >> 1), (int)(grp & 1u), j - grp * g.vh);
+            }
+            team_barrier(qs, size, ++phase, spin_limit);
+            if (want_p)
+                for (uint32_t j = rank * blockDim.x + threadIdx.x; j < 2u * g.vh;
+                     j += size * blockDim.x)
+                    psum += to_fixed((double)site_plaquettes(R, j));
+        }
+        if (SITE && want_p) team_add(R, ACC_PLAQ, rank, psum);
+        if (want_l) team_polyakov<SITE>(R, segs, rank, size);
+        if ((SITE && want_p) || want_l) team_barrier(qs, size, ++phase, spin_limit);
+        // the sums are complete; the next ones start after further barriers,
+        // which rank 0 reaches when it has taken these
+        if (rows && rank == 0u) {
+            unsigned long long tp = 0ull, tl = 0ull;
+            for (uint32_t j = threadIdx.x; j < (uint32_t)kBuckets; j += blockDim.x) {
+                tp += __hip_atomic_exchange(bucket(R.acc, ACC_PLAQ, j), 0ull, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+                tl += __hip_atomic_exchange(bucket(R.acc, ACC_POLY, j), 0ull, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+            }
+            tp = block_sum_u64(tp);
+            tl = block_sum_u64(tl);
+            if (threadIdx.x == 0) {
+                const double p = want_p ? from_fixed(tp) / (12.0 * (double)g.vh) : 0.0;
+                const double l = want_l ? from_fixed(tl) / ((double)g.nx * g.ny * g.nz) : 0.0;
+                double *row = hist + 3 * ((size_t)row0 + (uint32_t)i);
+                row[0] = p;
+                row[1] = l;
+                row[2] = fabs(l);
+            }
+        }
+    }
+}
+
+// Counters past the launch's sweeps; the team cleared for the next launch.
+__global__ void team_epilogue_kernel(Counters *c, int ns, int flags, TeamState *ts)
+{
+    if (!(flags & 16)) {
+        c->sweep += (uint32_t)ns;
+        if (flags & 4) *row_counter(c, (flags & 8) != 0) += (uint32_t)ns;
+    }
+    ts->target = ts->join = ts->size = ts->bar = 0u;
+}
+
 __global__ void xcc_probe_kernel(uint32_t *mask)
 {
     if (threadIdx.x == 0) atomicOr(mask, 1u << xcc_id());
@@ -1828,6 +2082,27 @@ hipError_t launch_queue_sweeps(const Ens &e, const QueuePlan &plan, const uint32
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(queue_epilogue_kernel, dim3(1, 1, e.nrep), dim3(1), 0, stream, e.reps, plan,
                        qs);
+    return hipGetLastError();
+}
+
+hipError_t launch_team_sweeps(const Ens &e, int ns, int n_or, uint64_t seed, int reunit_every,
+                              bool site, int flags, double *hist, QueueState *qs,
+                              uint32_t spin_limit, hipStream_t stream)
+{
+    if (ns <= 0) return hipSuccess;
+    // one workgroup per 256-link tile (at most 20, see kTeamMaxVh) on each XCD
+    const dim3 grid(8u * e.rep0->nblocks), block(256);
+    if (site)
+        hipLaunchKernelGGL(team_sweeps_kernel<true>, grid, block, 0, stream, *e.rep0, ns, n_or,
+                           e.poly_s, lo32(seed), hi32(seed), reunit_every, flags, hist, qs,
+                           spin_limit);
+    else
+        hipLaunchKernelGGL(team_sweeps_kernel<false>, grid, block, 0, stream, *e.rep0, ns, n_or,
+                           e.poly_s, lo32(seed), hi32(seed), 0, flags, hist, qs, spin_limit);
+    hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(team_epilogue_kernel, dim3(1), dim3(1), 0, stream, e.rep0->cnt, ns, flags,
+                       &qs->team);
     return hipGetLastError();
 }
 

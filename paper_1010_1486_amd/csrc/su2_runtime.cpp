@@ -309,6 +309,7 @@ public:
     hipGraphExec_t gexec = nullptr;
     int32_t g_nsweeps = 0;
     int32_t g_reunit = 0;  // reunitarisation period baked into the graph (0: none)
+    bool g_bounded = false;   // the graph's launches hold bounded waits (check_queue)
     bool rows_graph = false;  // enqueue() is being captured: rows on the graph's counter
     MarchShape march{};       // the LDS-staged pass's layout (cfg.march_R > 0)
     int64_t g_rows_cap = 0;   // history rows the capture's buffer holds (0: no history)
@@ -520,6 +521,51 @@ public:
         return !f64 && !cfg.queue && cfg.small && max_vh <= kSmallMaxVh;
     }
 
+    // Whole sweeps by a team of workgroups on one XCD: single lattices whose
+    // launch was not set, between the sizes that one workgroup and those that
+    // the whole chip runs faster.
+    bool team_path(int32_t ns, int mode) const
+    {
+        return n == 1 && !f64 && auto_launch && mode != SU2_LEARNED &&
+               max_vh <= (ns > 1 ? kTeamMaxVh : kTeamLoneMaxVh) &&
+               (mode == SU2_KP_OR || max_vh >= kTeamHeatbathMinVh);
+    }
+
+    // site sums (and the reunitarisation in the launch) where small_path() would
+    // run; else reunitarisation sweeps end with the launches of enqueue()
+    int enqueue_team(int32_t ns, int mode, int32_t reunit_every, int meas, double *hist, int gflag)
+    {
+        const bool want_p = hist && (meas & SU2_MEAS_PLAQ), want_l = hist && (meas & SU2_MEAS_POLY);
+        const int flags = (want_p ? 1 : 0) | (want_l ? 2 : 0) | (hist ? 4 | gflag : 0);
+        const bool site = mode == SU2_KP && small_path();
+        const int nor = mode == SU2_KP_OR ? n_or : 0;
+        queue_used = true;  // its bounded waits raise the same flag
+        const uint32_t sweep0 = sweep;
+        for (int32_t i = 0; i < ns;) {
+            // per launch, sweeps whose barriers the 32-bit arrival count holds;
+            // without site sums up to the next reunitarisation sweep, then that one
+            const uint32_t j = sweep0 + (uint32_t)i;
+            int32_t k = std::min(ns - i, 4096);
+            if (reunit_every > 0 && !site)
+                k = std::min<int32_t>(k, reunit_every - 1 - (int32_t)(j % (uint32_t)reunit_every));
+            if (k > 0) {
+                HIP_TRY(launch_team_sweeps(ens(), k, nor, seed, reunit_every, site, flags, hist,
+                                           d_qs(), spin_limit, stream));
+            } else {
+                k = 1;
+                HIP_TRY(launch_team_sweeps(ens(), 1, nor, seed, 0, false, 16, nullptr, d_qs(),
+                                           spin_limit, stream));
+                HIP_TRY(reunitarize_launch());
+                if (want_p) HIP_TRY(plaquette_launch());
+                if (want_l) HIP_TRY(polyakov_launch());
+                HIP_TRY(launch_sweep_end(ens(), flags, hist, stream));
+            }
+            i += k;
+        }
+        sweep += (uint32_t)ns;
+        return SU2_OK;
+    }
+
     // Workgroups of the persistent queue launch: the grid cap if set, else
     // as many as the device holds at once.
     // (at least one workgroup per queue: workgroups go to the XCDs in turn)
@@ -626,6 +672,8 @@ public:
         if (cfg.queue && !f64 && !per_pass)
             return enqueue_queue(ns, tab, reunit_every, meas, hist);
         const int gflag = rows_graph ? 8 : 0;
+        if (team_path(ns, mode) && !(reunit_fused && reunit_every > 0))
+            return enqueue_team(ns, mode, reunit_every, meas, hist, gflag);
         if (small_path() && !per_pass) {
             const int flags = (hist && (meas & SU2_MEAS_PLAQ) ? 1 : 0) |
                               (hist && (meas & SU2_MEAS_POLY) ? 2 : 0) | (hist ? 4 | gflag : 0);
@@ -681,10 +729,14 @@ public:
         if (hist) HIP_TRY(launch_set_counter(ens(), 0, 0, 32, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         const uint32_t s0 = sweep;
+        const bool used0 = queue_used;
         HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
         rows_graph = true;
+        queue_used = false;
         rc = enqueue(ns, mode, reunit_every, meas, hist, false);
         rows_graph = false;
+        const bool bounded = queue_used;  // the recorded launches hold bounded waits
+        queue_used = used0;
         hipGraph_t gr = nullptr;
         hipError_t e = hipStreamEndCapture(stream, &gr);
         sweep = s0;  // capturing ran nothing
@@ -701,6 +753,7 @@ public:
         }
         graph = gr;
         g_nsweeps = ns;
+        g_bounded = bounded;
         g_reunit = reunit_every > 0 ? reunit_every : 0;
         g_rows_cap = hist ? hist_rows : 0;
         g_rows_next = 0;
@@ -721,6 +774,7 @@ public:
                                         std::to_string(g_rows_next) + ".." +
                                         std::to_string(g_rows_next + (int64_t)count * g_nsweeps - 1) +
                                         " but dev_history holds " + std::to_string(g_rows_cap));
+        if (g_bounded && count > 0) queue_used = true;
         for (int32_t i = 0; i < count; ++i) HIP_TRY(hipGraphLaunch(gexec, stream));
         sweep += (uint32_t)(count * g_nsweeps);
         if (g_rows_cap > 0) g_rows_next += (int64_t)count * g_nsweeps;

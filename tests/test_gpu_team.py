@@ -1,0 +1,87 @@
+"""Sweeps of single lattices by a team of workgroups on one XCD (V/2 up to 5120,
+launch not set): links and sums are bit for bit those of the whole-sweep kernel
+(V/2 <= 2048) and of the pass launches, for every sweep kind, under capture, and
+with several lattices in flight on streams of their own."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import announce
+
+pytestmark = pytest.mark.gpu
+
+OR = 2  # SU2_KP_OR
+
+
+def run(su2, dims, mode, reunit, ns, launch, n_or=1):
+    with su2.Lattice(dims, 2.3, 19, su2.SU2_HOT) as lat:
+        if launch:
+            lat.set_launch(*launch)
+        lat.set_hb_overrelax(n_or)
+        lat.set_sweep(1)
+        lat.heatbath_sweep(1, mode)
+        h = lat.sweep_measure(ns, mode, reunit, 3).cpu().numpy()
+        lat.heatbath_sweep(0, mode)
+        return lat.get_links(), h, lat.sweep
+
+
+# V/2 320 and 512 (the heat bath in one workgroup), 520 (the first in a team), up to
+# 2048 sums per site, ragged last tiles, 5120 (the largest), and past it
+@pytest.mark.parametrize("dims", [[4, 4, 4, 10], [8, 8, 8, 2], [2, 2, 10, 26], [8, 8, 8, 8], [2, 2, 10, 102],
+                                  [10, 6, 14, 8], [16, 16, 8, 4], [16, 16, 10, 4],
+                                  [16, 16, 12, 4]],
+                         ids=["320", "512", "520", "2048", "2040", "3360", "4096", "5120", "6144"])
+@pytest.mark.parametrize("mode,reunit,ns,n_or", [(0, 3, 7, 0), (0, 0, 2, 0), (OR, 2, 5, 2),
+                                                 (OR, 1, 2, 0)])
+def test_team_equals_the_set_launch(su2, dims, mode, reunit, ns, n_or):
+    announce(f"team sweeps dims={dims} mode={mode}")
+    small = mode == 0 and np.prod(dims) <= 4096
+    got = run(su2, dims, mode, reunit, ns, None, n_or)
+    want = run(su2, dims, mode, reunit, ns, (256, 1 if small else 1 | 4), n_or)
+    np.testing.assert_array_equal(got[0], want[0])
+    np.testing.assert_array_equal(got[1], want[1])
+    assert got[2] == want[2] == 2 + ns
+
+
+def test_team_replays_and_many_sweeps(su2):
+    import torch
+    announce("team sweeps: replay, more sweeps than one launch takes")
+    dims = [6, 8, 6, 8]
+    with torch.cuda.stream(torch.cuda.Stream()):
+        lat = su2.Lattice(dims, 2.3, 5, su2.SU2_HOT)
+    hist = torch.zeros((12, 3), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    lat.capture(4, su2.SU2_KP, 2, 3, hist)
+    for k in range(3):
+        lat.replay(1)
+        torch.cuda.synchronize()  # the program's own work between replays
+        hist[4 * k:4 * k + 4].clone().sum().item()
+    with su2.Lattice(dims, 2.3, 5, su2.SU2_HOT) as ref:
+        ref.set_launch(256, 1)
+        h = ref.sweep_measure(12, su2.SU2_KP, 2, 3).cpu().numpy()
+        np.testing.assert_array_equal(hist.cpu().numpy(), h)
+        np.testing.assert_array_equal(lat.get_links(), ref.get_links())
+        ref.heatbath_sweep(4100)
+        lat.heatbath_sweep(4100)
+        np.testing.assert_array_equal(lat.get_links(), ref.get_links())
+    lat.close()
+
+
+def test_teams_on_several_streams(su2):
+    import torch
+    announce("team sweeps: 12 lattices in flight")
+    dims = [[8, 8, 8, 8], [10, 10, 8, 10], [4, 6, 8, 10]] * 4
+    lats = []
+    for k, d in enumerate(dims):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            lats.append(su2.Lattice(d, 2.0 + 0.05 * k, k, su2.SU2_HOT))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for lat in lats:
+            lat.heatbath_sweep(20)
+    torch.cuda.synchronize()
+    for k, (d, lat) in enumerate(zip(dims, lats)):
+        with su2.Lattice(d, 2.0 + 0.05 * k, k, su2.SU2_HOT) as ref:
+            ref.set_launch(256, 1 | 4)
+            ref.heatbath_sweep(60)
+            np.testing.assert_array_equal(lat.get_links(), ref.get_links())
+        lat.close()
