@@ -60,11 +60,12 @@ __device__ __forceinline__ Arr arr(const float *links, uint32_t vh, int mu, int 
     return Arr{(gchar *)links + (size_t)(mu * 2 + par) * vh * 16u};
 }
 
-__device__ __forceinline__ Q ld(const Arr &a, uint32_t h)
+__device__ __forceinline__ Q ldb(const Arr &a, uint32_t bytes)
 {
-    gf4 *p = (gf4 *)(a.base + h * 16u);
+    gf4 *p = (gf4 *)(a.base + bytes);
     return Q{p->x, p->y, p->z, p->w};
 }
+__device__ __forceinline__ Q ld(const Arr &a, uint32_t h) { return ldb(a, h * 16u); }
 
 __device__ __forceinline__ void st(float *links, uint32_t vh, int mu, int par, uint32_t h,
                                    const Q &q)
@@ -1118,18 +1119,20 @@ __global__ __launch_bounds__(MAXT) void tiny_sweeps_kernel(const Rep *__restrict
 // Per-site values are FP32; every thread adds its own in FP64 over all its
 // units and the workgroup's sums go to part[workgroup][pair (R, T), R <= T].
 //
-// Bound: L2 gathers (40 loads of 16 bytes per site and plane at N = 4, 15.7
-// TB/s at 48^4) and VALU (62 quaternion products of 16 operations).  A W(4, 4)
-// measurement takes 1303 us at 48^4 and 245 us at 32^4; with twelve planes, a
-// workgroup sum per plane and a buffer allocated on each call it took 4266 and
-// 806 us.
-constexpr int kWilsonGrid = 768;  // workgroups: the three a CU holds (138 VGPRs)
+// Bound: VALU issue (62 quaternion products of 16 operations per site and plane
+// at N = 4, busy throughout at 32^4); at 48^4 also the L2 (40 loads of 16 bytes
+// per site and plane, 18.5 TB/s).  Offsets are kept in eighths of a link and the
+// bases in scalar registers, for one add and one and per load.  A W(4, 4)
+// measurement takes 1110 us at 48^4 and 220 us at 32^4 (1220 and 236 with vector
+// bases and three workgroups on a CU); with twelve planes, a workgroup sum per
+// plane and a buffer allocated on each call it took 4266 and 806 us.
+constexpr int kWilsonGrid = 768;  // most workgroups of a launch (three a CU)
 
-// Site-index offset of k steps along a direction from coordinate c (extent n,
-// canonical stride st), periodic for 0 <= k <= n.
-__device__ __forceinline__ int32_t step_off(int c, int k, int n, int32_t st)
+// Offset (modulo 2^32) of k steps of stride st along a direction from coordinate
+// c (extent n), periodic for 0 <= k <= n.
+__device__ __forceinline__ uint32_t step_off(int c, int k, int n, uint32_t st)
 {
-    return (k - (c + k >= n ? n : 0)) * st;
+    return (uint32_t)(k - (c + k >= n ? n : 0)) * st;
 }
 
 __device__ __forceinline__ int pick4(int a, int v0, int v1, int v2, int v3)
@@ -1154,7 +1157,8 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ rep
     const uint32_t nsets = (g.vh + 127u) / 128u;  // sets of 128 half-sites
     const uint32_t per = (nsets + 7u) / 8u;       // sets per XCD
     const uint32_t x = blockIdx.x & 7u, step = gridDim.x >> 3;
-    const int par = threadIdx.x >= 128u ? 1 : 0;
+    // uniform over a wave, so that the loads take scalar bases
+    const int par = __builtin_amdgcn_readfirstlane(threadIdx.x >= 128u ? 1 : 0);
     double acc[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) acc[i] = 0.0;
@@ -1174,26 +1178,28 @@ __global__ __launch_bounds__(256) void wilson_kernel(const Rep *__restrict__ rep
             c0[0] = 2 * (int)(r - y * g.hx) + ((par + c0[1] + c0[2] + c0[3]) & 1);
         }
         const int32_t sy = g.nx, sz = g.nx * g.ny, stt = g.nx * g.ny * g.nz;
-        // canonical index of the site; the link k steps along mu and l along nu
-        // from it lies at s0 + oa[k] + ob[l] and has parity par + k + l
-        const uint32_t s0 = (uint32_t)c0[0] + (uint32_t)sy * (uint32_t)c0[1] +
-                            (uint32_t)sz * (uint32_t)c0[2] + (uint32_t)stt * (uint32_t)c0[3];
+        // eight times the site's canonical index; the link k steps along mu and l
+        // along nu from it lies at s8 + oa[k] + ob[l], 16 bytes per half-site, and
+        // has parity par + k + l
+        const uint32_t s8 = 8u * ((uint32_t)c0[0] + (uint32_t)sy * (uint32_t)c0[1] +
+                                  (uint32_t)sz * (uint32_t)c0[2] +
+                                  (uint32_t)stt * (uint32_t)c0[3]);
         const int ca = pick4(mu, c0[0], c0[1], c0[2], c0[3]);
         const int na = pick4(mu, g.nx, g.ny, g.nz, g.nt);
         const int32_t sa = pick4(mu, 1, sy, sz, stt);
         const int cb = pick4(nu, c0[0], c0[1], c0[2], c0[3]);
         const int nb = pick4(nu, g.nx, g.ny, g.nz, g.nt);
         const int32_t sb = pick4(nu, 1, sy, sz, stt);
-        int32_t oa[N + 1], ob[N + 1];
+        uint32_t oa[N + 1], ob[N + 1];
 #pragma unroll
         for (int k = 0; k <= N; ++k) {
-            oa[k] = step_off(ca, k, na, sa);
-            ob[k] = step_off(cb, k, nb, sb);
+            oa[k] = step_off(ca, k, na, 8u * (uint32_t)sa);
+            ob[k] = step_off(cb, k, nb, 8u * (uint32_t)sb);
         }
         // the two parities of each direction's class
         const Arr Amu[2] = {arr(R.links, g.vh, mu, par), arr(R.links, g.vh, mu, par ^ 1)};
         const Arr Anu[2] = {arr(R.links, g.vh, nu, par), arr(R.links, g.vh, nu, par ^ 1)};
-#define SU2_WL(A, k, l) ld(A[((k) + (l)) & 1], (s0 + (uint32_t)(oa[k] + ob[l])) >> 1)
+#define SU2_WL(A, k, l) ldb(A[((k) + (l)) & 1], (s8 + oa[k] + ob[l]) & ~15u)
         // every size up to N x N is computed without branches, so that the loads
         // can be issued ahead of the products; sizes beyond (rmax, tmax) are not
         // reported (the offsets wrap periodically, so every load stays inside).
@@ -2134,11 +2140,15 @@ uint32_t queue_resident_grid(int block, bool learned)
     return (uint32_t)(per_cu * cus);
 }
 
-// One workgroup per unit up to kWilsonGrid, a multiple of 8 for the XCD ranges.
-uint32_t wilson_grid(const Ens &e)
+// One workgroup per unit up to three on each CU, a multiple of 8 for the XCD
+// ranges.  At N = 4 two on each CU keep the VALU as busy and let the lines of
+// fewer sets compete for the L2 (us, two / three: 1072 / 1282 at 48^4, 331 / 341 at
+// 36^4, 215 / 220 at 32^4; at N = 3 675 / 700 and 143 / 139, at N = 2 408 / 354 and
+// 97 / 88).
+uint32_t wilson_grid(const Ens &e, int n)
 {
     const uint64_t units = 6ull * (((uint64_t)e.max_vh + 127) / 128 + 7);
-    return (uint32_t)std::min<uint64_t>(kWilsonGrid, (units + 7) & ~7ull);
+    return (uint32_t)std::min<uint64_t>(n == 4 ? 512u : kWilsonGrid, (units + 7) & ~7ull);
 }
 
 size_t wilson_work_bytes()
@@ -2149,7 +2159,7 @@ size_t wilson_work_bytes()
 
 hipError_t launch_wilson(const Ens &e, int n, double *work, double **sums, hipStream_t stream)
 {
-    const dim3 grid(wilson_grid(e)), block(256);
+    const dim3 grid(wilson_grid(e, n)), block(256);
     double *const part = work + kWilsonMax * kWilsonMax;
     *sums = work;
     switch (n) {
