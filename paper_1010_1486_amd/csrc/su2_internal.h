@@ -220,6 +220,12 @@ constexpr uint32_t kTinyMaxVh = 312;
 // is the faster (us per sweep, one workgroup / team: V/2 432 20.0 / 21.7, 648
 // 24.5 / 21.4); further figures at team_sweeps_kernel.
 constexpr uint32_t kTeamMaxVh = 5120, kTeamLoneMaxVh = 4096, kTeamHeatbathMinVh = 513;
+// Batches up to this many of their workgroups on an XCD, as the teams of one XCD
+// slow each other down (us per sweep, teams / pass launches: 16 x 8^4 32.1 / 38.1, 32 x
+// 8^4 39.7 / 39.2; with an over-relaxation sweep 32 x 6^4, load 12, 47.7 / 67.1, 32 x
+// 8^3 x 4, load 16, 81.0 / 67.0), and the heat bath past five tiles (16 x 8^3 x 4 33.3 /
+// 31.8 in one workgroup with the plaquette; 16 x 8^4 36.3 / 56.1).
+constexpr uint32_t kTeamLoad = 16, kTeamLoadOverrelax = 12, kTeamBatchHeatbathMinVh = 1281;
 
 // Everything a launch needs to address an ensemble on the device.
 struct Ens {
@@ -298,15 +304,16 @@ hipError_t launch_queue_sweeps(const Ens &e, const QueuePlan &plan, const uint32
                                uint64_t seed, int block, uint32_t grid, int grain, bool snake,
                                double *hist, const float *table, QueueState *qs,
                                uint32_t spin_limit, hipStream_t stream);
-// ns sweeps (each the heat bath, then n_or over-relaxation sweeps) of a single
-// FP32 lattice by a team of workgroups on one XCD, followed by a launch that
-// advances the counters and clears the team.  site: sums in per-site fixed
+// ns sweeps (each the heat bath, then n_or over-relaxation sweeps) of every FP32
+// lattice by a team of up to `width` workgroups on one XCD each, followed by a
+// launch that advances the counters and clears the teams.  site: sums in per-site fixed
 // point and the reunitarisation as launch_small_sweeps; else per workgroup of
 // 256 links as the pass launches, without reunitarisation.  flags: 1, 2, 4, 8
 // as launch_small_sweeps, 16 the passes alone (no sums, rows or sweep advance).
-hipError_t launch_team_sweeps(const Ens &e, int ns, int n_or, uint64_t seed, int reunit_every,
-                              bool site, int flags, double *hist, QueueState *qs,
-                              uint32_t spin_limit, hipStream_t stream);
+hipError_t launch_team_sweeps(const Ens &e, uint32_t width, int ns, int n_or, uint64_t seed,
+                              int reunit_every, bool site, int flags, double *hist,
+                              QueueState *qs, TeamState *teams, uint32_t spin_limit,
+                              hipStream_t stream);
 // Bit mask of the XCC ids that run workgroups of a large launch (one-time
 // probe of the current device; synchronous).
 hipError_t probe_xcc_mask(uint32_t *mask);

@@ -1496,9 +1496,10 @@ __global__ void queue_epilogue_kernel(const Rep *__restrict__ reps, QueuePlan pl
 
 // ------------------------------------------------------------- XCD team
 // Whole sweeps of one lattice in one launch by the workgroups of one XCD, with
-// a barrier among them after every pass.  The launch brings gridDim / 8
-// workgroups to each XCD; the XCD of the first one takes the lattice, the
-// others leave.  The team is whoever of that XCD came before its first
+// a barrier among them after every pass.  The launch brings `width` workgroups
+// per lattice to each XCD; the XCD of the first one takes the lattice (of a
+// batch's replica r XCD r mod 8, if it comes soon), the others leave.  The team
+// is whoever of that XCD came before its first
 // workgroup closed it (when all expected ones were there, or after a bounded
 // wait), so a barrier only ever waits for workgroups that are running, whatever
 // else occupies the GPU; the 256-link tiles are dealt out by rank.  Ordering is
@@ -1517,13 +1518,18 @@ __device__ __forceinline__ uint32_t team_load(const uint32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Rank in the team (~0u: not in it) and its size, in every thread.
-__device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t &size)
+// Rank in the team (~0u: not in it) and its size, in every thread.  want:
+// workgroups that make it whole; home: the XCD that should take it (-1: any).
+__device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t want, int home,
+                                              uint32_t &size)
 {
     __shared__ uint32_t s_rank, s_size;
     if (threadIdx.x == 0) {
         const uint32_t me = xcc_id() + 1u;
         uint32_t rank = 0xFFFFFFFFu, n = 0u, old = 0u;
+        if (home >= 0 && me != (uint32_t)home + 1u)
+            for (int i = 0; i < 64 && team_load(&ts->target) == 0u; ++i)
+                __builtin_amdgcn_s_sleep(4);
         __hip_atomic_compare_exchange_strong(&ts->target, &old, me, __ATOMIC_RELAXED,
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (old == 0u || old == me) {
@@ -1532,7 +1538,6 @@ __device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t &size)
             if (!(j & kTeamClosed)) {
                 rank = j;
                 if (j == 0u) {
-                    const uint32_t want = gridDim.x >> 3;
                     for (int i = 0; i < 64 && team_load(&ts->join) < want; ++i)
                         __builtin_amdgcn_s_sleep(4);
                     n = __hip_atomic_fetch_or(&ts->join, kTeamClosed, __ATOMIC_RELAXED,
@@ -1552,15 +1557,15 @@ __device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t &size)
 }
 
 // Barrier number `phase` (from 1) of the team; every wait is bounded.
-__device__ __forceinline__ void team_barrier(QueueState *qs, uint32_t size, uint32_t phase,
-                                             uint32_t spin_limit)
+__device__ __forceinline__ void team_barrier(QueueState *qs, TeamState *ts, uint32_t size,
+                                             uint32_t phase, uint32_t spin_limit)
 {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t goal = size * phase;
-        __hip_atomic_fetch_add(&qs->team.bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (uint32_t i = 0; team_load(&qs->team.bar) < goal; ++i) {
+        __hip_atomic_fetch_add(&ts->bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (uint32_t i = 0; team_load(&ts->bar) < goal; ++i) {
             if (i > spin_limit) {
                 __hip_atomic_store(&qs->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
@@ -1666,15 +1671,22 @@ __device__ __forceinline__ void team_polyakov(const Rep &R, int segs, uint32_t r
     }
 }
 
-template <bool SITE>
-__global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_or, int segs,
-                                                          uint32_t k0, uint32_t k1,
-                                                          int reunit_every, int flags,
-                                                          double *__restrict__ hist,
-                                                          QueueState *qs, uint32_t spin_limit)
+// BATCH: workgroups [8 width r, 8 width (r + 1)) bring replica r's.
+template <bool SITE, bool BATCH>
+__global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R0, const Rep *__restrict__ reps,
+                                                          int nrep, uint32_t width, int ns,
+                                                          int n_or, int segs, uint32_t k0,
+                                                          uint32_t k1, int reunit_every,
+                                                          int flags, double *__restrict__ hist,
+                                                          QueueState *qs, TeamState *teams,
+                                                          uint32_t spin_limit)
 {
+    const uint32_t r = BATCH ? blockIdx.x / (8u * width) : 0u;
+    const Rep &R = BATCH ? reps[r] : R0;
+    if (BATCH && (blockIdx.x >> 3) - r * width >= R.nblocks) return;
+    TeamState *const ts = teams + r;
     uint32_t size;
-    const uint32_t rank = team_join(&qs->team, size);
+    const uint32_t rank = team_join(ts, R.nblocks, BATCH ? (int)(r & 7u) : -1, size);
     if (rank == 0xFFFFFFFFu) return;
     const Geom &g = R.g;
     const uint32_t sweep0 = R.cnt->sweep, row0 = *row_counter(R.cnt, (flags & 8) != 0);
@@ -1695,7 +1707,7 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_o
                     team_pass_any<false, SITE>(R, mu, par, measure, rank, size, sweep, k0, k1, psum);
                 else if constexpr (!SITE)
                     team_pass_any<true, SITE>(R, mu, par, measure, rank, size, sweep, k0, k1, psum);
-                team_barrier(qs, size, ++phase, spin_limit);
+                team_barrier(qs, ts, size, ++phase, spin_limit);
             }
         }
         if (reunit) {
@@ -1704,7 +1716,7 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_o
                 const uint32_t grp = j / g.vh;
                 reunit_link(R, (int)(grp >> 1), (int)(grp & 1u), j - grp * g.vh);
             }
-            team_barrier(qs, size, ++phase, spin_limit);
+            team_barrier(qs, ts, size, ++phase, spin_limit);
             if (want_p)
                 for (uint32_t j = rank * blockDim.x + threadIdx.x; j < 2u * g.vh;
                      j += size * blockDim.x)
@@ -1712,7 +1724,7 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_o
         }
         if (SITE && want_p) team_add(R, ACC_PLAQ, rank, psum);
         if (want_l) team_polyakov<SITE>(R, segs, rank, size);
-        if ((SITE && want_p) || want_l) team_barrier(qs, size, ++phase, spin_limit);
+        if ((SITE && want_p) || want_l) team_barrier(qs, ts, size, ++phase, spin_limit);
         // the sums are complete; the next ones start after further barriers,
         // which rank 0 reaches when it has taken these
         if (rows && rank == 0u) {
@@ -1728,7 +1740,7 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_o
             if (threadIdx.x == 0) {
                 const double p = want_p ? from_fixed(tp) / (12.0 * (double)g.vh) : 0.0;
                 const double l = want_l ? from_fixed(tl) / ((double)g.nx * g.ny * g.nz) : 0.0;
-                double *row = hist + 3 * ((size_t)row0 + (uint32_t)i);
+                double *row = hist + 3 * (((size_t)row0 + (uint32_t)i) * (uint32_t)nrep + r);
                 row[0] = p;
                 row[1] = l;
                 row[2] = fabs(l);
@@ -1738,8 +1750,13 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R, int ns, int n_o
 }
 
 // Counters past the launch's sweeps; the team cleared for the next launch.
-__global__ void team_epilogue_kernel(Counters *c, int ns, int flags, TeamState *ts)
+__global__ void team_epilogue_kernel(const Rep *__restrict__ reps, int nrep, int ns, int flags,
+                                     TeamState *teams)
 {
+    const int r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (r >= nrep) return;
+    Counters *const c = reps[r].cnt;
+    TeamState *const ts = teams + r;
     if (!(flags & 16)) {
         c->sweep += (uint32_t)ns;
         if (flags & 4) *row_counter(c, (flags & 8) != 0) += (uint32_t)ns;
@@ -2091,24 +2108,24 @@ hipError_t launch_queue_sweeps(const Ens &e, const QueuePlan &plan, const uint32
     return hipGetLastError();
 }
 
-hipError_t launch_team_sweeps(const Ens &e, int ns, int n_or, uint64_t seed, int reunit_every,
-                              bool site, int flags, double *hist, QueueState *qs,
-                              uint32_t spin_limit, hipStream_t stream)
+hipError_t launch_team_sweeps(const Ens &e, uint32_t width, int ns, int n_or, uint64_t seed,
+                              int reunit_every, bool site, int flags, double *hist,
+                              QueueState *qs, TeamState *teams, uint32_t spin_limit,
+                              hipStream_t stream)
 {
     if (ns <= 0) return hipSuccess;
-    // one workgroup per 256-link tile (at most 20, see kTeamMaxVh) on each XCD
-    const dim3 grid(8u * e.rep0->nblocks), block(256);
-    if (site)
-        hipLaunchKernelGGL(team_sweeps_kernel<true>, grid, block, 0, stream, *e.rep0, ns, n_or,
-                           e.poly_s, lo32(seed), hi32(seed), reunit_every, flags, hist, qs,
-                           spin_limit);
-    else
-        hipLaunchKernelGGL(team_sweeps_kernel<false>, grid, block, 0, stream, *e.rep0, ns, n_or,
-                           e.poly_s, lo32(seed), hi32(seed), 0, flags, hist, qs, spin_limit);
+    const dim3 grid(8u * width * (uint32_t)e.nrep), block(256);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, stream, e.rep0 ? *e.rep0 : Rep{}, e.reps,
+                           e.nrep, width, ns, n_or, e.poly_s, lo32(seed), hi32(seed),
+                           site ? reunit_every : 0, flags, hist, qs, teams, spin_limit);
+    };
+    if (e.rep0) site ? go(team_sweeps_kernel<true, false>) : go(team_sweeps_kernel<false, false>);
+    else site ? go(team_sweeps_kernel<true, true>) : go(team_sweeps_kernel<false, true>);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(team_epilogue_kernel, dim3(1), dim3(1), 0, stream, e.rep0->cnt, ns, flags,
-                       &qs->team);
+    hipLaunchKernelGGL(team_epilogue_kernel, dim3(nblk(e.nrep, 64)), dim3(64), 0, stream, e.reps,
+                       e.nrep, ns, flags, teams);
     return hipGetLastError();
 }
 

@@ -333,10 +333,21 @@ public:
     static size_t rep_bytes() { return align_up(kRepScratch, 256); }
     // A batch's result slots lie side by side behind the replicas' scratch, so
     // that the host reads them in one copy; a single lattice's are in its own.
-    static size_t results_bytes(int n) { return n > 1 ? (size_t)n * kResultSlots * 8 : 0; }
+    static size_t results_bytes(int n)
+    {
+        return n > 1 ? align_up((size_t)n * kResultSlots * 8, 256) : 0;
+    }
     static size_t scratch_need(int n, const std::vector<std::array<int32_t, 4>> &d)
     {
-        return descr_bytes(n) + 2 * bmap_bytes(n, d) + (size_t)n * rep_bytes() + results_bytes(n);
+        return descr_bytes(n) + 2 * bmap_bytes(n, d) + (size_t)n * rep_bytes() +
+               results_bytes(n) + team_bytes(n);
+    }
+    // a batch's teams (team_sweeps_kernel) follow the result slots
+    static size_t team_bytes(int n) { return n > 1 ? (size_t)n * sizeof(TeamState) : 0; }
+    TeamState *d_teams() const
+    {
+        return n > 1 ? reinterpret_cast<TeamState *>(rep_scratch(n) + results_bytes(n))
+                     : &d_qs()->team;
     }
 
     Rep *d_reps() const { return reinterpret_cast<Rep *>(scratch); }
@@ -521,15 +532,21 @@ public:
         return !f64 && !cfg.queue && cfg.small && max_vh <= kSmallMaxVh;
     }
 
-    // Whole sweeps by a team of workgroups on one XCD: single lattices whose
+    // Whole sweeps by a team of workgroups on one XCD per lattice, where the
     // launch was not set, between the sizes that one workgroup and those that
     // the whole chip runs faster.
     bool team_path(int32_t ns, int mode) const
     {
-        return n == 1 && !f64 && auto_launch && mode != SU2_LEARNED &&
-               max_vh <= (ns > 1 ? kTeamMaxVh : kTeamLoneMaxVh) &&
-               (mode == SU2_KP_OR || max_vh >= kTeamHeatbathMinVh);
+        if (f64 || !auto_launch || mode == SU2_LEARNED ||
+            max_vh > (ns > 1 ? kTeamMaxVh : kTeamLoneMaxVh))
+            return false;
+        const bool over = mode == SU2_KP_OR;
+        if (n == 1) return over || max_vh >= kTeamHeatbathMinVh;
+        return (uint64_t)((n + 7) / 8) * team_width() <= (over ? kTeamLoadOverrelax : kTeamLoad) &&
+               (over || max_vh >= kTeamBatchHeatbathMinVh);
     }
+    // one workgroup per 256-link tile of the largest lattice
+    uint32_t team_width() const { return (max_vh + 255u) / 256u; }
 
     // site sums (and the reunitarisation in the launch) where small_path() would
     // run; else reunitarisation sweeps end with the launches of enqueue()
@@ -549,12 +566,12 @@ public:
             if (reunit_every > 0 && !site)
                 k = std::min<int32_t>(k, reunit_every - 1 - (int32_t)(j % (uint32_t)reunit_every));
             if (k > 0) {
-                HIP_TRY(launch_team_sweeps(ens(), k, nor, seed, reunit_every, site, flags, hist,
-                                           d_qs(), spin_limit, stream));
+                HIP_TRY(launch_team_sweeps(ens(), team_width(), k, nor, seed, reunit_every, site,
+                                           flags, hist, d_qs(), d_teams(), spin_limit, stream));
             } else {
                 k = 1;
-                HIP_TRY(launch_team_sweeps(ens(), 1, nor, seed, 0, false, 16, nullptr, d_qs(),
-                                           spin_limit, stream));
+                HIP_TRY(launch_team_sweeps(ens(), team_width(), 1, nor, seed, 0, false, 16,
+                                           nullptr, d_qs(), d_teams(), spin_limit, stream));
                 HIP_TRY(reunitarize_launch());
                 if (want_p) HIP_TRY(plaquette_launch());
                 if (want_l) HIP_TRY(polyakov_launch());
@@ -1748,7 +1765,10 @@ int su2_batch_init(su2_batch **out, int32_t n, const int32_t *dims, const double
     E.bmap_off = Ensemble::descr_bytes(n);
     E.qmap_off = E.bmap_off + Ensemble::bmap_bytes(n, E.dims);
     E.rep_off = E.qmap_off + Ensemble::bmap_bytes(n, E.dims);
-    if ((rc = E.upload()) || (rc = E.init(std::vector<int>(starts, starts + n)))) {
+    if (n > 1) e = hipMemset(E.d_teams(), 0, Ensemble::team_bytes(n));
+    if (e != hipSuccess) rc = fail(SU2_EHIP, std::string("teams: ") + hipGetErrorString(e));
+    if (e != hipSuccess || (rc = E.upload()) ||
+        (rc = E.init(std::vector<int>(starts, starts + n)))) {
         E.release();
         delete b;
         return rc;

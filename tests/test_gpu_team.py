@@ -1,7 +1,7 @@
-"""Sweeps of single lattices by a team of workgroups on one XCD (V/2 up to 5120,
+"""Sweeps of small lattices by teams of workgroups, one XCD each (V/2 up to 5120,
 launch not set): links and sums are bit for bit those of the whole-sweep kernel
-(V/2 <= 2048) and of the pass launches, for every sweep kind, under capture, and
-with several lattices in flight on streams of their own."""
+(V/2 <= 2048) and of the pass launches, for every sweep kind, under capture, with
+several lattices in flight on streams of their own, and in batches."""
 import numpy as np
 import pytest
 
@@ -85,3 +85,32 @@ def test_teams_on_several_streams(su2):
             ref.heatbath_sweep(60)
             np.testing.assert_array_equal(lat.get_links(), ref.get_links())
         lat.close()
+
+
+@pytest.mark.parametrize("n,dims", [(2, [[8, 8, 8, 8], [4, 4, 4, 6]]), (11, [[8, 8, 8, 6]]),
+                                    (7, [[10, 10, 8, 10], [6, 6, 6, 8], [4, 4, 4, 4]]),
+                                    (16, [[16, 16, 4, 4], [6, 6, 6, 6]]),
+                                    (17, [[16, 16, 4, 4], [6, 6, 6, 6]]),
+                                    (32, [[6, 6, 6, 6]])],
+                         ids=["2-mixed", "11", "7-mixed", "16-mixed", "17-mixed", "32"])
+@pytest.mark.parametrize("mode,reunit", [(0, 3), (0, 0), (OR, 2)])
+def test_team_batches_equal_the_set_launch(su2, n, dims, mode, reunit):
+    import torch
+    announce(f"team batch n={n} dims={dims} mode={mode}")
+    stream = torch.cuda.Stream()
+    dims = [dims[r % len(dims)] for r in range(n)]
+    small = mode == 0 and max(np.prod(d) for d in dims) <= 4096
+    out = []
+    for launch in (None, (256, 1 if small else 1 | 4)):
+        with torch.cuda.stream(stream), su2.Batch(dims, np.linspace(1.8, 2.8, n),
+                                                  [su2.SU2_HOT] * n, 3) as b:
+            if launch:
+                b.set_launch(*launch)
+            b.sweep(1, mode)
+            h = b.sweep_measure(7, mode, reunit, 3).cpu().numpy()
+            b.capture(2, mode)
+            b.replay(2)
+            out.append((h, [b.get_links(r) for r in range(n)]))
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    for got, want in zip(out[0][1], out[1][1]):
+        np.testing.assert_array_equal(got, want)
