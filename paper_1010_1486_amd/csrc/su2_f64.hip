@@ -193,8 +193,11 @@ __global__ __launch_bounds__(256) void pass64_kernel(Rep R, int par, uint32_t k0
                                                      int remap, int reverse)
 {
     const Geom &g = R.g;
-    const uint32_t blk = logical_block(blockIdx.x, gridDim.x, remap, reverse);
-    const uint32_t gid = blk * blockDim.x + threadIdx.x;
+    const uint32_t nblk = gridDim.x, dim = blockDim.x;
+    su2rt::args_first(nblk, par, k0, k1, remap, reverse, dim, R.g.vh, R.cnt, R.links, R.replica,
+                   R.beta_d);
+    const uint32_t blk = logical_block(blockIdx.x, nblk, remap, reverse);
+    const uint32_t gid = blk * dim + threadIdx.x;
     double meas = 0.0;
     if (gid < g.vh) {
         const uint32_t sweep = *(const __attribute__((address_space(4))) uint32_t *)&R.cnt->sweep;

@@ -7,6 +7,15 @@
 
 namespace su2rt {
 
+// Loads kernel arguments into scalar registers here, at the top of a kernel, in
+// one round.  Left to itself the compiler loads them branch by branch, and a
+// short pass waits for each round in turn.  us per sweep, before / now: SU(2)
+// 18 x 12 x 10 x 14 with three over-relaxations 130 / 121, FP64 12^4 52.5 / 50.3, SU(3)
+// 12^4 71.2 / 66.9; with the batch's descriptor in one round as well, 64 learned
+// replicas 346 / 329, 32 x 16^4 198 / 193.
+template <class T> __device__ __forceinline__ void arg_first(T v) { asm volatile("" ::"s"(v)); }
+template <class... T> __device__ __forceinline__ void args_first(T... v) { (arg_first(v), ...); }
+
 // FP64 sum over the block; the result is valid in thread 0.  Fixed order.
 __device__ __forceinline__ double block_sum(double v)
 {

@@ -243,13 +243,16 @@ __device__ __forceinline__ const float *load_table_lds(float4 *stab4, const floa
 // is a kernel argument, so the first neighbour address waits for one load
 // less (us per pass, loaded / argument: 8^4 4.35 / 4.03, 16^4 4.74 / 4.41, 32^4
 // 13.2 / 12.3); sums and links are pass_kernel's.
-template <int MU, bool MEASURE, bool OR, bool NORM>
+template <int MU, bool MEASURE, bool OR, bool NORM, bool LOOP>
 __global__ __launch_bounds__(256) void single_pass_kernel(Rep R, uint32_t total, int par,
                                                           uint32_t k0, uint32_t k1, int remap,
                                                           int reverse)
 {
-    for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) {
-        const uint32_t gid = logical_block(b, total, remap, reverse) * blockDim.x + threadIdx.x;
+    const uint32_t dim = blockDim.x;
+    su2rt::args_first(total, par, k0, k1, remap, reverse, dim, R.g.vh, R.cnt, R.links, R.replica,
+                   R.beta);
+    auto tile = [&](uint32_t b) {
+        const uint32_t gid = logical_block(b, total, remap, reverse) * dim + threadIdx.x;
         float meas = 0.0f;
         int acc = -1;
         if (gid < R.g.vh) {
@@ -260,10 +263,17 @@ __global__ __launch_bounds__(256) void single_pass_kernel(Rep R, uint32_t total,
                                                       acc);
         }
         if (MEASURE) block_accumulate((double)meas, R.acc, ACC_PLAQ, b);
-    }
+    };
+    if constexpr (LOOP)
+        for (uint32_t b = blockIdx.x; b < total; b += gridDim.x) tile(b);
+    else
+        tile(blockIdx.x);
 }
 
-template <int MU, bool MEASURE, bool LEARNED, bool OR = false, bool NORM = false>
+// Memory that the kernel only reads, as words for scalar loads.
+typedef const __attribute__((address_space(4))) uint32_t cword;
+
+template <int MU, bool MEASURE, bool LEARNED, bool OR, bool NORM, bool LOOP>
 __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
                                                    const uint32_t *__restrict__ bmap,
                                                    const uint2 *__restrict__ amap,
@@ -274,7 +284,9 @@ __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
     // LEARNED: the spline table in LDS (filled once per workgroup)
     __shared__ float4 stab4[LEARNED ? 1 + kNNRows * kNNRow / 4 : 1];
     const float *ltab = LEARNED ? load_table_lds(stab4, table) : nullptr;
-    for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
+    const uint32_t dim = blockDim.x;
+    args_first(reps, bmap, amap, total, par, k0, k1, remap, reverse, dim);
+    auto tile = [&](uint32_t i) {
         // A reversed pass over a batch takes the replicas, too, in reverse order
         // (the workgroup ids in groups of 8, which keeps each on its XCD), and so
         // starts on what the pass before left in the caches: 39 x 32^3 x Nt
@@ -283,22 +295,32 @@ __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
         const uint32_t b = flip ? total - 8u - (i & ~7u) + (i & 7u) : i;
         uint32_t r, local;
         if (amap) {
-            const uint2 a = amap[b];
-            if (a.x == 0xFFFFFFFFu) continue;  // padding workgroup (uniform)
-            r = a.x;
-            local = a.y;
+            cword *const a = (cword *)(amap + b);
+            r = a[0];
+            local = a[1];
+            if (r == 0xFFFFFFFFu) return;  // padding workgroup (uniform)
         } else {
-            r = bmap ? bmap[b] : 0u;
-            local = b - reps[r].first_block;
+            r = bmap ? *(cword *)(bmap + b) : 0u;
+            local = b;
         }
-        const Rep &R = reps[r];
-        if (local >= R.nblocks) continue;  // padding workgroup (uniform)
+        // the whole descriptor in one round of scalar loads
+        cword *const d = (cword *)(reps + r);
+        uint32_t words[sizeof(Rep) / 4];
+#pragma unroll
+        for (uint32_t k = 0; k < sizeof(Rep) / 4; ++k) words[k] = d[k];
+        Rep R;
+        __builtin_memcpy(&R, words, sizeof(Rep));
         const Geom &g = R.g;
+        args_first(g.nx, g.ny, g.nz, g.nt, g.vh, g.hx, g.P, g.PZ, g.wy, g.wz, g.wt, g.lg_tz, g.lg_tt,
+                   g.ntz, g.m_P, g.s_P, g.m_hx, g.s_hx, g.m_ntz, g.s_ntz, R.links, R.cnt, R.beta,
+                   R.replica, R.first_block, R.nblocks);
+        if (!amap) local -= R.first_block;
+        if (local >= R.nblocks) return;  // padding workgroup (uniform)
         // the blocks of an XCD-affine replica run in order on one XCD
         const int rev = reverse && !flip;
         const uint32_t blk = amap ? (rev ? R.nblocks - 1u - local : local)
                                   : logical_block(local, R.nblocks, remap, rev);
-        const uint32_t gid = blk * blockDim.x + threadIdx.x;
+        const uint32_t gid = blk * dim + threadIdx.x;
         float meas = 0.0f;
         int acc = -1;
         if (gid < g.vh) {
@@ -314,12 +336,16 @@ __global__ __launch_bounds__(256) void pass_kernel(const Rep *__restrict__ reps,
             const unsigned long long mp = __ballot(acc >= 0);
             const unsigned long long ma = __ballot(acc == 1);
             if ((threadIdx.x & 63) == 0) {
-                const uint32_t wb = b * (blockDim.x >> 6) + (threadIdx.x >> 6);
+                const uint32_t wb = b * (dim >> 6) + (threadIdx.x >> 6);
                 if (mp) atomicAdd(bucket(R.acc, ACC_PROPOSED, wb), (unsigned long long)__popcll(mp));
                 if (ma) atomicAdd(bucket(R.acc, ACC_ACCEPTED, wb), (unsigned long long)__popcll(ma));
             }
         }
-    }
+    };
+    if constexpr (LOOP)
+        for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) tile(i);
+    else
+        tile(blockIdx.x);
 }
 
 // ------------------------------------------------------- streaming floor
@@ -1881,24 +1907,30 @@ void launch_pass_mn(const Ens &e, int par, uint64_t seed, bool measure, const fl
     const int rev = cfg.snake ? par : 0;
     if constexpr (!LEARNED)
         if (e.rep0) {
-            if (measure)
-                hipLaunchKernelGGL((single_pass_kernel<MU, true, OR, NORM>), dim3(grid),
-                                   dim3(block), 0, stream, *e.rep0, total, par, lo32(seed),
-                                   hi32(seed), (int)cfg.xcd_remap, rev);
-            else
-                hipLaunchKernelGGL((single_pass_kernel<MU, false, OR, NORM>), dim3(grid),
-                                   dim3(block), 0, stream, *e.rep0, total, par, lo32(seed),
-                                   hi32(seed), (int)cfg.xcd_remap, rev);
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, stream, *e.rep0, total, par,
+                                   lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev);
+            };
+            if (grid < total) {
+                if (measure) go(single_pass_kernel<MU, true, OR, NORM, true>);
+                else go(single_pass_kernel<MU, false, OR, NORM, true>);
+            } else {
+                if (measure) go(single_pass_kernel<MU, true, OR, NORM, false>);
+                else go(single_pass_kernel<MU, false, OR, NORM, false>);
+            }
             return;
         }
-    if (measure)
-        hipLaunchKernelGGL((pass_kernel<MU, true, LEARNED, OR, NORM>), dim3(grid),
-                           dim3(block), 0, stream, e.reps, e.bmap, e.amap, total, par,
-                           lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev, table);
-    else
-        hipLaunchKernelGGL((pass_kernel<MU, false, LEARNED, OR, NORM>), dim3(grid),
-                           dim3(block), 0, stream, e.reps, e.bmap, e.amap, total, par,
-                           lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev, table);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), 0, stream, e.reps, e.bmap, e.amap,
+                           total, par, lo32(seed), hi32(seed), (int)cfg.xcd_remap, rev, table);
+    };
+    if (grid < total) {
+        if (measure) go(pass_kernel<MU, true, LEARNED, OR, NORM, true>);
+        else go(pass_kernel<MU, false, LEARNED, OR, NORM, true>);
+    } else {
+        if (measure) go(pass_kernel<MU, true, LEARNED, OR, NORM, false>);
+        else go(pass_kernel<MU, false, LEARNED, OR, NORM, false>);
+    }
 }
 
 template <int MU, bool LEARNED, bool OR = false>

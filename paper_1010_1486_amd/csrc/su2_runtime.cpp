@@ -1765,7 +1765,7 @@ int su2_batch_init(su2_batch **out, int32_t n, const int32_t *dims, const double
     E.bmap_off = Ensemble::descr_bytes(n);
     E.qmap_off = E.bmap_off + Ensemble::bmap_bytes(n, E.dims);
     E.rep_off = E.qmap_off + Ensemble::bmap_bytes(n, E.dims);
-    if (n > 1) e = hipMemset(E.d_teams(), 0, Ensemble::team_bytes(n));
+    if (n > 1) e = hipMemsetAsync(E.d_teams(), 0, Ensemble::team_bytes(n), E.stream);
     if (e != hipSuccess) rc = fail(SU2_EHIP, std::string("teams: ") + hipGetErrorString(e));
     if (e != hipSuccess || (rc = E.upload()) ||
         (rc = E.init(std::vector<int>(starts, starts + n)))) {

@@ -15,6 +15,7 @@
 // products of SU(3) matrices compute two rows and complete the third the same
 // way.  Sums are FP64 per workgroup and 64-bit fixed point across workgroups.
 #include "su2_kcommon.h"
+#include <type_traits>
 #include "su3_internal.h"
 
 using namespace su2dev;
@@ -452,13 +453,20 @@ __device__ __forceinline__ float update_site3(const Lat3 &L, uint32_t gid, int p
     return MEASURE ? retr_mul(U, Alow) * (1.0f / 3.0f) : 0.0f;
 }
 
-template <int MU, bool MEASURE, bool OR>
+// The workgroups' order: of a single lattice, of a batch (replica = grid z), or
+// of a batch with each replica's workgroups on one XCD.
+enum Order3 { ORDER_SINGLE, ORDER_BATCH, ORDER_AFFINE };
+
+template <int MU, bool MEASURE, bool OR, int ORDER>
 __global__ __launch_bounds__(256) void su3_pass_kernel(Lat3 L0, int par, uint32_t k0,
                                                        uint32_t k1, uint32_t nblocks, int remap,
-                                                       int reverse, int affine)
+                                                       int reverse)
 {
-    uint32_t r, blk;
-    if (affine) {
+    const uint32_t dim = blockDim.x;
+    su2rt::args_first(nblocks, remap, reverse, par, dim, k0, k1, L0.g.vh, L0.ctr, L0.links,
+                   L0.replica, L0.beta);
+    uint32_t r = 0u, blk;
+    if (ORDER == ORDER_AFFINE) {
         // workgroups go to the XCDs in turn: XCD x runs replicas x, x + 8, ...
         // one after the other
         const uint32_t id = blockIdx.x + nblocks * blockIdx.z, k = id >> 3, slot = k / nblocks;
@@ -468,16 +476,17 @@ __global__ __launch_bounds__(256) void su3_pass_kernel(Lat3 L0, int par, uint32_
         if (reverse) blk = nblocks - 1u - blk;
     } else {
         // a reversed pass takes the replicas, too, in reverse order
-        r = reverse ? gridDim.z - 1u - blockIdx.z : blockIdx.z;
+        if (ORDER == ORDER_BATCH) r = reverse ? gridDim.z - 1u - blockIdx.z : blockIdx.z;
         blk = logical_block(blockIdx.x, nblocks, remap, reverse);
     }
-    const Lat3 L = rep3(L0, r);
-    const uint32_t gid = blk * blockDim.x + threadIdx.x;
+    // (a single lattice's coupling is L.beta, also that of a batch of one)
+    const Lat3 L = ORDER == ORDER_SINGLE ? L0 : rep3(L0, r);
+    // the sweep index lives on the device (uniform: a scalar load through the
+    // constant address space), so captured sweeps replay correctly
+    const uint32_t sweep = *(const __attribute__((address_space(4))) uint32_t *)L.ctr;
+    const uint32_t gid = blk * dim + threadIdx.x;
     float meas = 0.0f;
     if (gid < L.g.vh) {
-        // the sweep index lives on the device (uniform: a scalar load through
-        // the constant address space), so captured sweeps replay correctly
-        const uint32_t sweep = *(const __attribute__((address_space(4))) uint32_t *)L.ctr;
         meas = update_site3<MU, MEASURE, OR>(L, gid, par, sweep, k0, k1);
     }
     if (MEASURE) block_accumulate((double)meas, L.acc, A3_PLAQ, blockIdx.x);
@@ -654,12 +663,17 @@ void launch_pass_mu(const Lat3 &L, int par, uint32_t k0, uint32_t k1,
     const int affine = remap && L.nrep > 1 && (uint64_t)L.g.vh * 384u <= (12u << 20) &&
                        10u * nz8 <= 11u * L.nrep && nz8 <= 65535u;
     const dim3 grid(nb, 1, affine ? nz8 : L.nrep), block(cfg.block);
-    if (measure)
-        hipLaunchKernelGGL((su3_pass_kernel<MU, true, OR>), grid, block, 0, s, L, par, k0, k1, nb,
-                           remap, reverse, affine);
-    else
-        hipLaunchKernelGGL((su3_pass_kernel<MU, false, OR>), grid, block, 0, s, L, par, k0, k1, nb,
-                           remap, reverse, affine);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, s, L, par, k0, k1, nb, remap, reverse);
+    };
+    auto pick = [&](auto order) {
+        constexpr int O = decltype(order)::value;
+        if (measure) go(su3_pass_kernel<MU, true, OR, O>);
+        else go(su3_pass_kernel<MU, false, OR, O>);
+    };
+    if (L.nrep == 1) pick(std::integral_constant<int, ORDER_SINGLE>{});
+    else if (affine) pick(std::integral_constant<int, ORDER_AFFINE>{});
+    else pick(std::integral_constant<int, ORDER_BATCH>{});
 }
 
 template <bool OR>
