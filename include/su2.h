@@ -211,7 +211,7 @@ int su2_synchronize(su2_ctx *ctx);
  * the alternating (forward, backward) pass order, bit 2 = disable the
  * whole-sweep kernel for small lattices (by default, when every V/2 <= 2048,
  * one launch runs whole sweeps with one workgroup per lattice; an unset launch
- * of a single lattice or of a few replicas up to V/2 = 5120 with several
+ * of a single lattice or of a few replicas up to V/2 = 3072 with several
  * workgroups of one XCD per lattice, with the same results), bit 3 = run
  * sweeps as one persistent work-queue launch per call (every pass, the
  * reunitarisation and the measurements of all replicas, ordered per replica

@@ -213,19 +213,21 @@ constexpr uint32_t kSmallMaxVh = 2048;
 // Largest V/2 whose heat-bath sweeps keep the field in LDS (three threads per
 // link, at most 960, and 208 bytes of LDS per half-site within 64 KiB).
 constexpr uint32_t kTinyMaxVh = 312;
-// V/2 of the lattices whose sweeps a team of workgroups on one XCD runs.  Up to 20
-// tiles of 256 links; with more the barriers cost what the launches did.  From 16
-// on only calls of several sweeps: a lone one at 20 tiles took 47 us, its pass
-// launches 45.  The heat bath alone only past two tiles, up to which one workgroup
-// is the faster (us per sweep, one workgroup / team: V/2 432 20.0 / 21.7, 648
-// 24.5 / 21.4); further figures at team_sweeps_kernel.
-constexpr uint32_t kTeamMaxVh = 5120, kTeamLoneMaxVh = 4096, kTeamHeatbathMinVh = 513;
-// Batches up to this many of their workgroups on an XCD, as the teams of one XCD
-// slow each other down (us per sweep, teams / pass launches: 16 x 8^4 32.1 / 38.1, 32 x
-// 8^4 39.7 / 39.2; with an over-relaxation sweep 32 x 6^4, load 12, 47.7 / 67.1, 32 x
-// 8^3 x 4, load 16, 81.0 / 67.0), and the heat bath past five tiles (16 x 8^3 x 4 33.3 /
-// 31.8 in one workgroup with the plaquette; 16 x 8^4 36.3 / 56.1).
-constexpr uint32_t kTeamLoad = 16, kTeamLoadOverrelax = 12, kTeamBatchHeatbathMinVh = 1281;
+// V/2 of the lattices whose sweeps a team of workgroups on one XCD runs.  Up to 12
+// tiles of 256 links; with more the barriers cost what the launches do (us per
+// sweep, team / pass launches: 8^4 26.2 / 28.3, 16 x 16 x 8 x 4 27.2 / 29.4, a lone sweep
+// of it 44.9 / 43.2, 10^4 31.1 / 30.0).  The heat bath alone only past three tiles, up
+// to which one workgroup is as fast (one workgroup / team, with both measurements:
+// 6^4 26.7 / 28.4, 8^3 x 4 32.1 / 25.5).
+constexpr uint32_t kTeamMaxVh = 3072, kTeamHeatbathMinVh = 769;
+// Batches up to this many of the teams' workgroups on an XCD, as they slow each
+// other down: in the heat bath up to V/2 2048 kTeamLoadSmall, where one workgroup per
+// replica is the other form (us per sweep with the plaquette, teams / that: 5 x 8^4,
+// load 8, 29.9 / 55.1; 16 x 8^4, load 16, 35.0 / 55.0; 16 x 8^3 x 4, hence not below five
+// tiles, 33.3 / 31.1); else kTeamLoad, against pass launches (with an over-relaxation
+// sweep 32 x 6^4, load 12, 47.1 / 57.5; 5 x 10 x 10 x 8 x 8, load 13, 35.6 / 36.5, a lone
+// sweep of it 49.3 / 48.3).
+constexpr uint32_t kTeamLoad = 12, kTeamLoadSmall = 16, kTeamBatchHeatbathMinVh = 1281;
 
 // Everything a launch needs to address an ensemble on the device.
 struct Ens {

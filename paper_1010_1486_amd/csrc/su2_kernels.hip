@@ -1535,10 +1535,9 @@ __global__ void queue_epilogue_kernel(const Rep *__restrict__ reps, QueuePlan pl
 //
 // Bound: per pass the update's own latency and one barrier, which grows with
 // the workgroups (arrivals, and the acquires' L1 invalidations, about 90 ns
-// each).  us per heat-bath sweep, one workgroup or pass launches / team: 6^4
-// 24.5 / 21.4, 8^4 53.6 / 22.6, 10^4 33.9 / 28.9; with both measurements 25.7 /
-// 25.5, 55.1 / 27.3, 42.3 / 36.4; with an over-relaxation sweep 64.7 / 44.0,
-// 65.2 / 44.2, 66.2 / 56.7.  12^4 (41 tiles) with the plaquette 42 / 51.
+// each).  us per heat-bath sweep, one workgroup / pass launches / team: 8^4 54.0 /
+// 28.3 / 26.2, with both measurements 55.6 / 35.1 / 31.0; with an over-relaxation
+// sweep 6^4 - / 50.5 / 40.9, 8^4 - / 48.4 / 43.7.
 __device__ __forceinline__ uint32_t team_load(const uint32_t *p)
 {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -535,14 +535,13 @@ public:
     // Whole sweeps by a team of workgroups on one XCD per lattice, where the
     // launch was not set, between the sizes that one workgroup and those that
     // the whole chip runs faster.
-    bool team_path(int32_t ns, int mode) const
+    bool team_path(int mode) const
     {
-        if (f64 || !auto_launch || mode == SU2_LEARNED ||
-            max_vh > (ns > 1 ? kTeamMaxVh : kTeamLoneMaxVh))
-            return false;
+        if (f64 || !auto_launch || mode == SU2_LEARNED || max_vh > kTeamMaxVh) return false;
         const bool over = mode == SU2_KP_OR;
         if (n == 1) return over || max_vh >= kTeamHeatbathMinVh;
-        return (uint64_t)((n + 7) / 8) * team_width() <= (over ? kTeamLoadOverrelax : kTeamLoad) &&
+        const uint32_t most = !over && max_vh <= kSmallMaxVh ? kTeamLoadSmall : kTeamLoad;
+        return (uint64_t)((n + 7) / 8) * team_width() <= most &&
                (over || max_vh >= kTeamBatchHeatbathMinVh);
     }
     // one workgroup per 256-link tile of the largest lattice
@@ -689,7 +688,7 @@ public:
         if (cfg.queue && !f64 && !per_pass)
             return enqueue_queue(ns, tab, reunit_every, meas, hist);
         const int gflag = rows_graph ? 8 : 0;
-        if (team_path(ns, mode) && !(reunit_fused && reunit_every > 0))
+        if (team_path(mode) && !(reunit_fused && reunit_every > 0))
             return enqueue_team(ns, mode, reunit_every, meas, hist, gflag);
         if (small_path() && !per_pass) {
             const int flags = (hist && (meas & SU2_MEAS_PLAQ) ? 1 : 0) |

@@ -1,4 +1,4 @@
-"""Sweeps of small lattices by teams of workgroups, one XCD each (V/2 up to 5120,
+"""Sweeps of small lattices by teams of workgroups, one XCD each (V/2 up to 3072,
 launch not set): links and sums are bit for bit those of the whole-sweep kernel
 (V/2 <= 2048) and of the pass launches, for every sweep kind, under capture, with
 several lattices in flight on streams of their own, and in batches."""
@@ -24,12 +24,12 @@ def run(su2, dims, mode, reunit, ns, launch, n_or=1):
         return lat.get_links(), h, lat.sweep
 
 
-# V/2 320 and 512 (the heat bath in one workgroup), 520 (the first in a team), up to
-# 2048 sums per site, ragged last tiles, 5120 (the largest), and past it
-@pytest.mark.parametrize("dims", [[4, 4, 4, 10], [8, 8, 8, 2], [2, 2, 10, 26], [8, 8, 8, 8], [2, 2, 10, 102],
-                                  [10, 6, 14, 8], [16, 16, 8, 4], [16, 16, 10, 4],
-                                  [16, 16, 12, 4]],
-                         ids=["320", "512", "520", "2048", "2040", "3360", "4096", "5120", "6144"])
+# V/2 320 and 768 (the heat bath in one workgroup), 800 (in a team), up to 2048 sums
+# per site, ragged last tiles, 3072 (the largest), and past it
+@pytest.mark.parametrize("dims", [[4, 4, 4, 10], [2, 2, 12, 32], [2, 2, 10, 40], [8, 8, 8, 8],
+                                  [2, 2, 10, 102], [10, 6, 8, 10], [16, 16, 6, 4],
+                                  [10, 6, 14, 8]],
+                         ids=["320", "768", "800", "2048", "2040", "2400", "3072", "3360"])
 @pytest.mark.parametrize("mode,reunit,ns,n_or", [(0, 3, 7, 0), (0, 0, 2, 0), (OR, 2, 5, 2),
                                                  (OR, 1, 2, 0)])
 def test_team_equals_the_set_launch(su2, dims, mode, reunit, ns, n_or):
@@ -69,7 +69,7 @@ def test_team_replays_and_many_sweeps(su2):
 def test_teams_on_several_streams(su2):
     import torch
     announce("team sweeps: 12 lattices in flight")
-    dims = [[8, 8, 8, 8], [10, 10, 8, 10], [4, 6, 8, 10]] * 4
+    dims = [[8, 8, 8, 8], [10, 8, 8, 8], [4, 6, 8, 10]] * 4
     lats = []
     for k, d in enumerate(dims):
         with torch.cuda.stream(torch.cuda.Stream()):
@@ -88,7 +88,7 @@ def test_teams_on_several_streams(su2):
 
 
 @pytest.mark.parametrize("n,dims", [(2, [[8, 8, 8, 8], [4, 4, 4, 6]]), (11, [[8, 8, 8, 6]]),
-                                    (7, [[10, 10, 8, 10], [6, 6, 6, 8], [4, 4, 4, 4]]),
+                                    (7, [[10, 8, 8, 8], [6, 6, 6, 8], [4, 4, 4, 4]]),
                                     (16, [[16, 16, 4, 4], [6, 6, 6, 6]]),
                                     (17, [[16, 16, 4, 4], [6, 6, 6, 6]]),
                                     (32, [[6, 6, 6, 6]])],
