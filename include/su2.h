@@ -342,7 +342,8 @@ int su2_nn_set_data(su2_nn *nn, int64_t n, const float *alpha_host, const float 
 /* Data held: *n, and (if non-NULL) copies into host arrays of *n floats. */
 int su2_nn_get_data(su2_nn *nn, int64_t *n, float *alpha_host, float *a0_host);
 /* Mean NLL and its gradient (host float[2671]) over samples [offset,
- * offset + batch) (indices mod n).  Synchronous. */
+ * offset + batch) (indices mod n).  Synchronous.  SU2_EINVAL for a batch of
+ * 2^31 - 32768 or more, here and in training. */
 int su2_nn_loss_grad(su2_nn *nn, int64_t offset, int32_t batch, double *loss, float *grad_host);
 /* `steps` Adam steps on consecutive minibatches of the data (wrapping);
  * loss_history_host (may be NULL) receives each step's mean NLL.  Synchronous. */

@@ -2308,6 +2308,11 @@ int su2_nn_get_data(su2_nn *n, int64_t *count, float *alpha_host, float *a0_host
 
 static int nn_reserve_part(su2_nn *n, int batch)
 {
+    // the step kernel's sample index is an int that runs past the batch by up to
+    // one tile of every workgroup
+    const int most = INT32_MAX - nn_parts(INT32_MAX) * kNNTile;
+    if (batch > most)
+        return fail(SU2_EINVAL, "batch must be at most " + std::to_string(most));
     const int parts = nn_parts(batch);
     if (parts <= n->part_cap) return SU2_OK;
     if (n->b.part) (void)hipFree(n->b.part);
