@@ -143,10 +143,10 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
     __shared__ double gder[NNWAVES * 15 * 32];  // derivative rows of W3, per wave
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int j = lane & 15, q = lane >> 4;  // sample of the tile; 16-lane group
-    // the sample of this lane at a tile (a lane without one takes the first sample)
+    // the sample of this lane at a tile (a lane without one takes the batch's first)
     auto at = [&](int base) {
         const int b = base + 16 * wv + j;
-        int64_t i = b < batch ? offset + b : 0;
+        int64_t i = offset + (b < batch ? b : 0);
         if (i >= n) {  // offset < n, so one subtraction unless the batch wraps twice
             i -= n;
             if (i >= n) i %= n;
@@ -196,9 +196,10 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
     for (int base = (int)blockIdx.x * kNNTile; base < batch; base += (int)gridDim.x * kNNTile) {
         const int b = base + 16 * wv + j;
         const bool live = b < batch;
-        // a lane without a sample computes one that contributes nothing
-        const float f = live ? nn_feature(al) : 0.0f;
-        const float xv = live ? x0 : 0.0f;
+        // A lane without a sample repeats the batch's first one, with zero in place
+        // of its gradients: a product with them is zero, or the NaN that the sample
+        // itself gives
+        const float f = nn_feature(al), xv = x0;
         const int next = base + (int)gridDim.x * kNNTile;
         if (next < batch) {
             idx = at(next);
@@ -349,7 +350,7 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * t + 4 * q + v;
                 const float hm = H2[j * HS + m], a = c[v];
-                D2[j * HS + m] = a * (1.0f - hm * hm);
+                D2[j * HS + m] = live ? a * (1.0f - hm * hm) : 0.0f;
             }
         }
         wave_sync();
@@ -367,7 +368,7 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * t + 4 * q + v;
                 const float hm = H1[j * HS + m], a = c[v];
-                D1[j * HS + m] = a * (1.0f - hm * hm);
+                D1[j * HS + m] = live ? a * (1.0f - hm * hm) : 0.0f;
             }
         }
         if (q == 0) KB[j] = k;

@@ -1,7 +1,9 @@
-"""Edges of a training step of the learned proposal: the largest batch."""
+"""Edges of a training step of the learned proposal: the largest batch, weights that are not
+finite."""
 import numpy as np
 import pytest
 
+from oracle import nn_oracle as nn
 from tests.gpu_util import announce
 
 pytestmark = pytest.mark.gpu
@@ -28,3 +30,30 @@ def test_batch_past_the_sample_index_is_refused(su2, batch):
             assert e.value.code == su2.SU2_EINVAL
         np.testing.assert_array_equal(net.params, p)
         assert np.isfinite(net.loss_grad(0, 100)[0])
+
+
+def params(seed):
+    return (np.random.default_rng(seed).standard_normal(2671) * 0.1).astype(np.float32)
+
+
+# batches that end inside a tile of 64 samples (1, 36, 63 lanes with one), and whole tiles
+@pytest.mark.parametrize("batch", [1, 100, 127, 128, 700])
+@pytest.mark.parametrize("index", [0, 40, 64, 1090], ids=["W1", "b1", "W2", "b2"])
+def test_infinite_weights_saturate(su2, batch, index):
+    """An infinite weight of a hidden layer saturates its unit: loss and gradient are the oracle's,
+    finite wherever its are, also where lanes of the last tile have no sample."""
+    announce(f"nn infinite weight {index} batch {batch}")
+    p, (al, x) = params(5), samples(1000)
+    p[index] = np.inf
+    with su2.NN(params=p) as net:
+        net.set_data(al, x)
+        loss, g = net.loss_grad(0, batch)
+    wl, wg = nn.loss_and_grad(p, al[:batch].astype(np.float64), x[:batch].astype(np.float64))
+    np.testing.assert_array_equal(np.isfinite(g), np.isfinite(wg))
+    if np.isfinite(wl):
+        assert loss == pytest.approx(wl, rel=1e-5)
+    # per tensor, the bound that the gradient of finite weights has against the oracle
+    for lo, hi in ((0, 32), (32, 64), (64, 1088), (1088, 1120), (1120, 2624), (2624, 2671)):
+        w, ok = wg[lo:hi], np.isfinite(wg[lo:hi])
+        bound = 1e-3 * np.abs(w[ok]) + 1e-4 * np.linalg.norm(w[ok])
+        assert np.all(np.abs(g[lo:hi][ok] - w[ok]) <= bound), (lo, hi)
