@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
         if (64 * i + lane < 15 * 32) GD[64 * i + lane] = 0.0;
     for (int base = (int)blockIdx.x * kNNTile; base < batch; base += (int)gridDim.x * kNNTile) {
         const int b = base + 16 * wv + j;
-        const bool live = b < batch;
+        const bool live = b < batch, ragged = batch - base < kNNTile;  // (uniform)
         // A lane without a sample repeats the batch's first one, with zero in place
         // of its gradients: a product with them is zero, or the NaN that the sample
         // itself gives
@@ -350,9 +350,11 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * t + 4 * q + v;
                 const float hm = H2[j * HS + m], a = c[v];
-                D2[j * HS + m] = live ? a * (1.0f - hm * hm) : 0.0f;
+                D2[j * HS + m] = a * (1.0f - hm * hm);
             }
         }
+        if (ragged && !live)
+            for (int v = 0; v < 8; ++v) D2[j * HS + 16 * (v >> 2) + 4 * q + (v & 3)] = 0.0f;
         wave_sync();
         // back through layer 2: dz1 = (W2^T dz2) (1 - h1^2)
 #pragma unroll
@@ -368,9 +370,11 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
             for (int v = 0; v < 4; ++v) {
                 const int m = 16 * t + 4 * q + v;
                 const float hm = H1[j * HS + m], a = c[v];
-                D1[j * HS + m] = live ? a * (1.0f - hm * hm) : 0.0f;
+                D1[j * HS + m] = a * (1.0f - hm * hm);
             }
         }
+        if (ragged && !live)
+            for (int v = 0; v < 8; ++v) D1[j * HS + 16 * (v >> 2) + 4 * q + (v & 3)] = 0.0f;
         if (q == 0) KB[j] = k;
         wave_sync();
         // biases and W1, one sample after the other: FP32 products, FP64 sums.  Of the
