@@ -287,6 +287,7 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
         const float den = s + tt * om;
         const float num = dh * xi * xi + 2.0f * s * om + dl * (1.0f - xi) * (1.0f - xi);
         const float ell = 2.0f * logf(s) + logf(num) - 2.0f * logf(den);
+        const bool undefined = __any(ell != ell);  // (uniform)
         if (live && q == 0) gloss += (double)-(-0.69314718055994531f + ell);
 
         // d ell / d(s, xi, d_k, d_k+1)
@@ -380,7 +381,9 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
         // biases and W1, one sample after the other: FP32 products, FP64 sums.  Of the
         // 15 derivative rows of W3 a sample touches the two at its bin's ends:
         // the lower half of the wave adds row k - 1, the upper half row k, to
-        // sums in LDS (in sample order: the LDS serves a wave's adds in turn)
+        // sums in LDS (in sample order: the LDS serves a wave's adds in turn).  The
+        // other rows' products are zero times an activation: nothing but for a NaN,
+        // which shows in the sample's loss
         const int o3 = lane < 47 ? lane : 47;
         const float *const db = half ? D1 + m0 : D2 + m0;
         int row[16];
@@ -398,6 +401,11 @@ __global__ __launch_bounds__(256, 2) void nn_step_kernel(const float *__restrict
             gw1 += (double)(z * F[sm]);  // W1 in the upper lanes (the lower ones' is unused)
             // a row outside 0..14 reads inside the sample's record and is not added
             pr[sm] *= DO[sm * OS + 32 + row[sm]];
+        }
+        if (undefined && half == 0) {
+            float nil = 0.0f;
+            for (int sm = 0; sm < 16; ++sm) nil += H2[sm * HS + m0] * 0.0f;
+            for (int r = 0; r < 15; ++r) GD[r * 32 + m0] += (double)nil;
         }
 #pragma unroll
         for (int sm = 0; sm < 16; ++sm)

@@ -57,3 +57,18 @@ def test_infinite_weights_saturate(su2, batch, index):
         w, ok = wg[lo:hi], np.isfinite(wg[lo:hi])
         bound = 1e-3 * np.abs(w[ok]) + 1e-4 * np.linalg.norm(w[ok])
         assert np.all(np.abs(g[lo:hi][ok] - w[ok]) <= bound), (lo, hi)
+
+
+@pytest.mark.parametrize("batch", [1, 64, 700])
+def test_nan_activation_reaches_every_row(su2, batch):
+    """A NaN in the hidden layers makes every gradient of a weight NaN, among them those of
+    the derivative outputs that no sample's bin touches."""
+    announce(f"nn NaN weight batch {batch}")
+    p = params(5)
+    p[3] = np.nan  # W1
+    with su2.NN(params=p) as net:
+        net.set_data(*samples(1000))
+        loss, g = net.loss_grad(0, batch)
+        assert np.isnan(loss) and np.isnan(g[:2624]).all()
+        net.train(2, batch)
+        assert np.isnan(net.params[:2624]).all()
