@@ -227,8 +227,9 @@ int su2_synchronize(su2_ctx *ctx);
  * over-relaxation; SU2_LEARNED keeps the plain pass): workgroups of R =
  * tile_z full x-rows of an (x, y) plane walk T = tile_t planes along t
  * (R must divide Ny and T divide Nt, 2 <= R, R Nx/2 <= 256; SU2_EINVAL
- * otherwise, and with bit 3); it implies bit 2;
- * the traversal
+ * otherwise, and with bit 3); it implies bit 2; bit 8 = the unset launch, as
+ * if no launch had been set (with block 256, bit 0 alone beside it and grid_cap
+ * 0, else SU2_EINVAL; the tiles are then 8 x 8); the traversal
  * tile of (z, t) planes, tile_z x tile_t (powers of two <= 256, clipped to
  * divisors of Nz and Nt; 0 keeps the current value); grid_cap > 0 runs the
  * pass as a persistent grid of at most grid_cap workgroups looping over the
@@ -237,14 +238,17 @@ int su2_synchronize(su2_ctx *ctx);
  * 2^-28 fixed point instead of each workgroup's sum (differences ~1e-9).
  * Drops captured sweeps. */
 int su2_set_launch(su2_ctx *ctx, int block, int flags, int tile_z, int tile_t, int grid_cap);
-/* Current launch configuration (tiles as applied to this lattice's extents). */
+/* Current launch configuration (tiles as applied to this lattice's extents;
+ * flags bit 8 while no launch is set).  su2_set_launch of these values keeps
+ * it. */
 int su2_get_launch(su2_ctx *ctx, int *block, int *flags, int *tile_z, int *tile_t, int *grid_cap);
 
 /* Autotuner: times candidate launch configurations (block size, order flags,
  * traversal tile, persistent grid) on this lattice with sweeps of `mode` that
- * measure the plaquette (every candidate on 2 sweeps, the three fastest again
- * on 8; the faster of two timings each), restores links and counters
- * afterwards, and applies the fastest.  With a
+ * measure the plaquette (every candidate, the unset launch among them, on 2
+ * sweeps, the three fastest and the unset launch again on 8; the faster of two
+ * timings each), restores links and counters afterwards, and applies the
+ * fastest.  With a
  * cache_path (JSON lines, one entry per device and set of extents), a cached
  * choice is applied without timing and new choices are appended.
  * *best_us_per_sweep (may be NULL) receives its time per sweep. */

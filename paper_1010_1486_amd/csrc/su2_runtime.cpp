@@ -915,7 +915,10 @@ public:
     {
         if (block < 64 || block > 256 || (block % 64) != 0)
             return fail(SU2_EINVAL, "block must be 64, 128, 192 or 256");
-        if (flags < 0 || flags > 255) return fail(SU2_EINVAL, "flags must be in [0, 255]");
+        const bool unset = (flags & 256) != 0;
+        if (flags < 0 || flags > 511 || (unset && (flags != 257 || block != 256 || grid_cap)))
+            return fail(SU2_EINVAL, "flags must be in [0, 255], or 257 (the unset launch) with "
+                                    "block 256 and grid_cap 0");
         if (grid_cap < 0) return fail(SU2_EINVAL, "grid_cap must be >= 0");
         const bool march_on = (flags & 128) != 0;
         MarchShape ms{};
@@ -934,7 +937,8 @@ public:
             if ((rc = lg_of_tile(tile_z, lg_tz, &lz))) return rc;
             if ((rc = lg_of_tile(tile_t, lg_tt, &lt))) return rc;
         }
-        auto_launch = false;
+        if (unset) lz = lt = 3;
+        auto_launch = unset;
         cfg.pass_block = block;
         cfg.xcd_remap = (flags & 1) != 0;
         cfg.snake = (flags & 2) == 0;
@@ -1080,14 +1084,16 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
     const uint32_t sweep0 = sweep;
     const LaunchCfg cfg0 = cfg;
     const bool auto0 = auto_launch;
+    const MarchShape march0 = march;
     const uint32_t lz0 = lg_tz, lt0 = lg_tt;
-    // candidates: the whole-sweep kernel when the lattices are small enough,
-    // then the pass kernels over block sizes, traversal flags, tiles and
+    // candidates: the unset launch, which alone holds the teams of workgroups and
+    // the one-wave passes; the whole-sweep kernel when the lattices are small
+    // enough, then the pass kernels over block sizes, traversal flags, tiles and
     // persistent grid sizes
     struct Cand {
         int block, flags, tz, tt, grid;
     };
-    std::vector<Cand> cands;
+    std::vector<Cand> cands{{256, 257, 8, 8, 0}};
     const bool small_ok = !f64 && max_vh <= kSmallMaxVh && mode != SU2_KP_OR;
     if (small_ok) cands.push_back({256, 1, 8, 8, 0});
     const int no_small = small_ok ? 4 : 0;
@@ -1129,8 +1135,8 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
     // Trial sweeps measure the plaquette, as the benchmarked and most other
     // sweeps do (the fused measurement changes which launch is fastest); their
     // history rows go to a buffer of the autotuner's own.  Every candidate is
-    // timed on `trial_sweeps` sweeps, then the three fastest again on
-    // `final_sweeps`; each timing is the faster of two runs.
+    // timed on `trial_sweeps` sweeps, then the three fastest and the unset
+    // launch again on `final_sweeps`; each timing is the faster of two runs.
     const int final_sweeps = 8;
     double *thist = nullptr;
     if (e == hipSuccess) e = hipMalloc(&thist, (size_t)final_sweeps * (size_t)n * 3 * sizeof(double));
@@ -1157,7 +1163,8 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
         first.push_back({us, i});
     }
     std::sort(first.begin(), first.end());
-    for (size_t k = 0; k < first.size() && k < 3 && e == hipSuccess && !rc; ++k) {
+    for (size_t k = 0; k < first.size() && e == hipSuccess && !rc; ++k) {
+        if (k >= 3 && first[k].second != 0) continue;
         const Cand &c = cands[first[k].second];
         double us;
         if (!time_cand(c, final_sweeps, &us)) break;
@@ -1190,6 +1197,7 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
         // keep the launch configuration the ensemble had before
         cfg = cfg0;
         auto_launch = auto0;
+        march = march0;
         lg_tz = lz0;
         lg_tt = lt0;
         const int rc2 = upload();
@@ -1689,7 +1697,7 @@ static void get_launch(const Ensemble &E, int *block, int *flags, int *tile_z, i
         while ((1 << lg) < E.cfg.grain) ++lg;
         *flags = (E.cfg.xcd_remap ? 1 : 0) | (E.cfg.snake ? 0 : 2) | (E.cfg.small ? 0 : 4) |
                  (E.cfg.queue ? 8 : 0) | (lg << 4) | (E.cfg.affine ? 64 : 0) |
-                 (E.cfg.march_R ? 128 : 0);
+                 (E.cfg.march_R ? 128 : 0) | (E.auto_launch ? 256 : 0);
     }
     if (tile_z) *tile_z = E.cfg.march_R ? (int)E.cfg.march_R : 1 << E.geom[0].lg_tz;
     if (tile_t) *tile_t = E.cfg.march_R ? (int)E.cfg.march_T : 1 << E.geom[0].lg_tt;

@@ -591,7 +591,8 @@ class Lattice:
 
     def set_launch(self, block, flags=1, tile_z=0, tile_t=0, grid_cap=0):
         """flags: bit 0 XCD remap, bit 1 disables the alternating pass order, bit 2
-        disables the whole-sweep kernel of small lattices."""
+        disables the whole-sweep kernel of small lattices; 257 is the unset launch.
+        set_launch(**launch()) keeps the launch."""
         su2_set_launch(self.h, block, flags, tile_z, tile_t, grid_cap)
 
     def autotune(self, cache_path=None, mode=SU2_KP):
