@@ -867,6 +867,47 @@ public:
         }
     }
 
+    // Up to this many sites (FP32, FP64) the host rearranges the links itself, around
+    // one copy of the field: a launch less than through the staging buffer.  us of get +
+    // set, staging / host: FP32 4 x 4 x 4 x 8 47 / 23, 8^3 x 4 53 / 32, 8^4 61 / 44; FP64 6^4
+    // 56 / 35, 8 x 8 x 6 x 4 58 / 56, 8^3 x 4 62 / 68 (classes a multiple of 4 KB apart).
+    static constexpr size_t kHostExchangeSites[2] = {4096, 1400};
+    template <typename D, typename H>
+    int exchange_on_host(int r, bool set, H *host)
+    {
+        const int32_t *d = dims[r].data();
+        const size_t V = (size_t)volume_of(d), vh = V / 2, bytes = V * 16 * sizeof(D);
+        std::unique_ptr<D[]> field(new (std::nothrow) D[V * 16]);
+        if (!field)
+            return fail(SU2_ENOMEM, "host staging buffer of " + std::to_string(bytes) + " B");
+        if (!set) {
+            HIP_TRY(hipMemcpyAsync(field.get(), links[r], bytes, hipMemcpyDeviceToHost, stream));
+            HIP_TRY(hipStreamSynchronize(stream));
+        }
+        size_t s = 0;
+        for (int t = 0; t < d[3]; ++t)
+            for (int z = 0; z < d[2]; ++z)
+                for (int y = 0; y < d[1]; ++y)
+                    for (int x = 0; x < d[0]; ++x, ++s)
+                        for (size_t mu = 0; mu < 4; ++mu) {
+                            // a class is one array of four components per half-site in
+                            // FP32 and two arrays of pairs in FP64
+                            constexpr size_t m = sizeof(D) == sizeof(double) ? 2 : 4;
+                            D *const cls = &field[(mu * 2 + ((x + y + z + t) & 1)) * vh * 4];
+                            H *const out = host + (s * 4 + mu) * 4;
+                            for (size_t k = 0; k < 4; ++k) {
+                                D &v = cls[(k / m * vh + (s >> 1)) * m + k % m];
+                                if (set) v = (D)out[k];
+                                else out[k] = (H)v;
+                            }
+                        }
+        if (set) {
+            HIP_TRY(hipMemcpyAsync(links[r], field.get(), bytes, hipMemcpyHostToDevice, stream));
+            HIP_TRY(hipStreamSynchronize(stream));
+        }
+        return SU2_OK;
+    }
+
     // Host layout [t][z][y][x][mu][c] in H (float or double) <-> the device
     // layout in the ensemble's precision, one staging buffer at a time.
     template <typename H>
@@ -875,6 +916,9 @@ public:
         const size_t V = (size_t)volume_of(dims[r].data()), site = 16 * sizeof(H);
         if (!set)
             if (int rc = check_queue()) return rc;
+        if (V <= kHostExchangeSites[f64])
+            return f64 ? exchange_on_host<double>(r, set, host)
+                       : exchange_on_host<float>(r, set, host);
         if (int rc = reserve_stage(V * site)) return rc;
         const size_t chunk = stage_bytes / site;
         for (size_t s0 = 0; s0 < V; s0 += chunk) {
