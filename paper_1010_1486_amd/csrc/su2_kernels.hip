@@ -2090,11 +2090,26 @@ hipError_t launch_gauge(const Ens &e, float *G, uint64_t seed, hipStream_t strea
 static constexpr uint32_t tiny_lds(uint32_t vh) { return 13u * 16u * vh; }
 static_assert(tiny_lds(kTinyMaxVh) + 256 <= 65536, "64 KiB of LDS per workgroup");
 
+// Whether ns sweeps of a batch run in LDS.  They take three times the waves and most
+// of a CU's LDS, so where a CU gets more than one replica the kernel that leaves the
+// field in the caches overlaps more of them.  us of a call of 1 and of 20 sweeps, LDS /
+// caches: 256 x 4^4 23.6 / 27.7 and 168 / 294, 512 x 4^4 34.0 / 30.9 and 304 / 347, 1024 x 4^4
+// 53.8 / 33.5 and 568 / 369; 512 x 4 x 4 x 4 x 2 23.2 / 27.0 and 162 / 274, 1024 of it 33.5 /
+// 28.5 and 305 / 285.  Past V/2 256 the other kernel has idle lanes in its last wave:
+// 1024 x 6 x 6 x 4 x 4 79.5 / 78.7 and 871 / 1230.
+static bool tiny_fits(const Ens &e, int ns)
+{
+    if (e.max_vh > kTinyMaxVh) return false;
+    const uint32_t per_cu = ((uint32_t)e.nrep + 255u) / 256u;
+    if (per_cu == 1u || (per_cu == 2u && e.max_vh <= 64u)) return true;
+    return ns >= 16 && (e.max_vh > 256u || (per_cu == 2u && e.max_vh <= 128u));
+}
+
 hipError_t launch_small_sweeps(const Ens &e, int ns, uint64_t seed, int reunit_every, int flags,
                                double *hist, const float *table, hipStream_t stream)
 {
     if (ns <= 0) return hipSuccess;
-    if (!table && e.max_vh <= kTinyMaxVh) {
+    if (!table && tiny_fits(e, ns)) {
         const uint32_t vhp = (e.max_vh + 63u) & ~63u;
         const dim3 grid(e.nrep), tiny(3u * vhp);
         if (tiny.x <= 384u)
