@@ -446,8 +446,8 @@ int su2_test_index_map(const int32_t dims[4], int tile_z, int tile_t, int parity
 int su2_test_queue_plan(int32_t n, const int32_t *dims, int block, int32_t queues,
                         int32_t nsweeps, int32_t reunit_every, uint32_t first_sweep, int meas,
                         int rows, int64_t *items_out);
-/* Polls allowed per bounded wait of the batch's work-queue launches (default
- * 2^22).  A small value makes the waits run out on purpose: the launch then
+/* Polls allowed per bounded wait of the batch's work-queue and team launches
+ * (default 2^22).  A small value makes the waits run out on purpose: the launch then
  * drains normally and the next synchronising call returns SU2_EHIP. */
 int su2_test_batch_spin_limit(su2_batch *b, uint32_t polls);
 /* Learned-proposal update of n independent links (host float[n][4] staples V

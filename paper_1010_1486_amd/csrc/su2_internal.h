@@ -63,7 +63,8 @@ constexpr uint32_t kTeamClosed = 1u << 31;
 
 struct QueueState {
     uint32_t ticket[kMaxQueues][32];  // next item of queue q (own 128-byte line each)
-    uint32_t error;                   // nonzero: a bounded wait ran out or work was left over
+    uint32_t error;                   // queue: 1 a bounded wait ran out, 2 work was left over;
+                                      // teams: 3 a bounded wait ran out, 4 there was no team
     uint32_t pad0[31];
     TeamState team;
     int32_t rank[kMaxQueues];         // XCC id -> queue (-1: the XCD takes no work)
@@ -312,6 +313,8 @@ hipError_t launch_queue_sweeps(const Ens &e, const QueuePlan &plan, const uint32
 // point and the reunitarisation as launch_small_sweeps; else per workgroup of
 // 256 links as the pass launches, without reunitarisation.  flags: 1, 2, 4, 8
 // as launch_small_sweeps, 16 the passes alone (no sums, rows or sweep advance).
+// ns 0 with flag 16 only clears the teams, as after a call that failed between the
+// two launches.
 hipError_t launch_team_sweeps(const Ens &e, uint32_t width, int ns, int n_or, uint64_t seed,
                               int reunit_every, bool site, int flags, double *hist,
                               QueueState *qs, TeamState *teams, uint32_t spin_limit,
@@ -338,8 +341,8 @@ hipError_t launch_wilson(const Ens &e, int n, double *work, double **sums, hipSt
 // Workgroups of `block` threads of the queue kernel the device holds at once.
 uint32_t queue_resident_grid(int block, bool learned);
 // which: 1 set sweep, 2 set meas_idx, 4 zero all accumulators, 8 zero counts,
-// 16 zero the work-queue state (done counters; qs ticket and error), 32 set
-// graph_row.
+// 16 zero the state of queue and team launches (done counters; qs ticket, error
+// and team; the sums), 32 set graph_row.
 hipError_t launch_set_counter(const Ens &e, uint32_t sweep, uint32_t meas, int which,
                               hipStream_t stream, QueueState *qs = nullptr);
 // results[R_COUNTS..] = proposals, accepts (as uint64); reset if asked.

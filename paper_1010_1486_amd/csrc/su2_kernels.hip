@@ -642,6 +642,8 @@ __global__ __launch_bounds__(kBuckets) void set_counter_kernel(const Rep *__rest
             qs->team.target = qs->team.join = qs->team.size = qs->team.bar = 0u;
         }
     }
+    if (which & 16)  // a launch that gave up leaves sums behind
+        *bucket(R.acc, ACC_PLAQ, threadIdx.x) = *bucket(R.acc, ACC_POLY, threadIdx.x) = 0ull;
     if (which & 4)
         for (int a = 0; a < kNumAcc; ++a) *bucket(R.acc, a, threadIdx.x) = 0ull;
     else if (which & 8)
@@ -1543,10 +1545,15 @@ __device__ __forceinline__ uint32_t team_load(const uint32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ void team_fail(QueueState *qs)
+{
+    __hip_atomic_store(&qs->error, 3u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Rank in the team (~0u: not in it) and its size, in every thread.  want:
 // workgroups that make it whole; home: the XCD that should take it (-1: any).
-__device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t want, int home,
-                                              uint32_t &size)
+__device__ __forceinline__ uint32_t team_join(QueueState *qs, TeamState *ts, uint32_t want,
+                                              int home, uint32_t spin_limit, uint32_t &size)
 {
     __shared__ uint32_t s_rank, s_size;
     if (threadIdx.x == 0) {
@@ -1569,7 +1576,14 @@ __device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t want, int 
                                               __HIP_MEMORY_SCOPE_AGENT);
                     __hip_atomic_store(&ts->size, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 } else {
-                    while ((n = team_load(&ts->size)) == 0u) __builtin_amdgcn_s_sleep(2);
+                    for (uint32_t i = 0; (n = team_load(&ts->size)) == 0u; ++i) {
+                        if (i > spin_limit) {  // the others' barriers give up, too
+                            team_fail(qs);
+                            rank = 0xFFFFFFFFu;
+                            break;
+                        }
+                        __builtin_amdgcn_s_sleep(2);
+                    }
                 }
             }
         }
@@ -1581,7 +1595,8 @@ __device__ __forceinline__ uint32_t team_join(TeamState *ts, uint32_t want, int 
     return s_rank;
 }
 
-// Barrier number `phase` (from 1) of the team; every wait is bounded.
+// Barrier number `phase` (from 1) of the team.  Once a wait of the launch has run out
+// of polls the others end within 32.
 __device__ __forceinline__ void team_barrier(QueueState *qs, TeamState *ts, uint32_t size,
                                              uint32_t phase, uint32_t spin_limit)
 {
@@ -1592,9 +1607,10 @@ __device__ __forceinline__ void team_barrier(QueueState *qs, TeamState *ts, uint
         __hip_atomic_fetch_add(&ts->bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (uint32_t i = 0; team_load(&ts->bar) < goal; ++i) {
             if (i > spin_limit) {
-                __hip_atomic_store(&qs->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                team_fail(qs);
                 break;
             }
+            if ((i & 31u) == 31u && team_load(&qs->error)) break;
             __builtin_amdgcn_s_sleep(1);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -1711,7 +1727,8 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R0, const Rep *__r
     if (BATCH && (blockIdx.x >> 3) - r * width >= R.nblocks) return;
     TeamState *const ts = teams + r;
     uint32_t size;
-    const uint32_t rank = team_join(ts, R.nblocks, BATCH ? (int)(r & 7u) : -1, size);
+    const uint32_t rank =
+        team_join(qs, ts, R.nblocks, BATCH ? (int)(r & 7u) : -1, spin_limit, size);
     if (rank == 0xFFFFFFFFu) return;
     const Geom &g = R.g;
     const uint32_t sweep0 = R.cnt->sweep, row0 = *row_counter(R.cnt, (flags & 8) != 0);
@@ -1774,9 +1791,10 @@ __global__ __launch_bounds__(256) void team_sweeps_kernel(Rep R0, const Rep *__r
     }
 }
 
-// Counters past the launch's sweeps; the team cleared for the next launch.
+// Counters past the launch's sweeps; the team, if it ran them, cleared for the
+// next launch.
 __global__ void team_epilogue_kernel(const Rep *__restrict__ reps, int nrep, int ns, int flags,
-                                     TeamState *teams)
+                                     QueueState *qs, TeamState *teams)
 {
     const int r = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (r >= nrep) return;
@@ -1786,6 +1804,8 @@ __global__ void team_epilogue_kernel(const Rep *__restrict__ reps, int nrep, int
         c->sweep += (uint32_t)ns;
         if (flags & 4) *row_counter(c, (flags & 8) != 0) += (uint32_t)ns;
     }
+    if (ns && ts->size == 0u)
+        __hip_atomic_store(&qs->error, 4u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     ts->target = ts->join = ts->size = ts->bar = 0u;
 }
 
@@ -2159,19 +2179,20 @@ hipError_t launch_team_sweeps(const Ens &e, uint32_t width, int ns, int n_or, ui
                               QueueState *qs, TeamState *teams, uint32_t spin_limit,
                               hipStream_t stream)
 {
-    if (ns <= 0) return hipSuccess;
     const dim3 grid(8u * width * (uint32_t)e.nrep), block(256);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, stream, e.rep0 ? *e.rep0 : Rep{}, e.reps,
                            e.nrep, width, ns, n_or, e.poly_s, lo32(seed), hi32(seed),
                            site ? reunit_every : 0, flags, hist, qs, teams, spin_limit);
     };
-    if (e.rep0) site ? go(team_sweeps_kernel<true, false>) : go(team_sweeps_kernel<false, false>);
-    else site ? go(team_sweeps_kernel<true, true>) : go(team_sweeps_kernel<false, true>);
+    if (ns > 0) {
+        if (e.rep0) site ? go(team_sweeps_kernel<true, false>) : go(team_sweeps_kernel<false, false>);
+        else site ? go(team_sweeps_kernel<true, true>) : go(team_sweeps_kernel<false, true>);
+    }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL(team_epilogue_kernel, dim3(nblk(e.nrep, 64)), dim3(64), 0, stream, e.reps,
-                       e.nrep, ns, flags, teams);
+                       e.nrep, ns, flags, qs, teams);
     return hipGetLastError();
 }
 

@@ -315,7 +315,8 @@ public:
     int64_t g_rows_cap = 0;   // history rows the capture's buffer holds (0: no history)
     int64_t g_rows_next = 0;  // first row the next replay writes
     // work queue
-    bool queue_used = false;           // queue launches since the last error check
+    bool queue_used = false;           // queue or team launches since the last error check
+    bool teams_stale = false;          // a team launch failed before the teams were cleared
     uint32_t spin_limit = 1u << 22;    // polls per bounded wait
     uint32_t queue_grid_auto[2] = {0, 0};  // resident workgroups (heat bath, learned)
     int queue_nq = 1;                      // queues (XCDs)
@@ -569,6 +570,18 @@ public:
         const bool site = mode == SU2_KP && small_path();
         const int nor = mode == SU2_KP_OR ? n_or : 0;
         queue_used = true;  // its bounded waits raise the same flag
+        auto launch = [&](int k, int every, bool st, int fl, double *rows) {
+            hipError_t e = hipSuccess;
+            if (teams_stale)
+                e = launch_team_sweeps(ens(), team_width(), 0, 0, seed, 0, false, 16, nullptr,
+                                       d_qs(), d_teams(), spin_limit, stream);
+            teams_stale = true;
+            if (e == hipSuccess)
+                e = launch_team_sweeps(ens(), team_width(), k, nor, seed, every, st, fl, rows,
+                                       d_qs(), d_teams(), spin_limit, stream);
+            teams_stale = e != hipSuccess;
+            return e;
+        };
         const uint32_t sweep0 = sweep;
         for (int32_t i = 0; i < ns;) {
             // per launch, sweeps whose barriers the 32-bit arrival count holds;
@@ -578,12 +591,10 @@ public:
             if (reunit_every > 0 && !site)
                 k = std::min<int32_t>(k, reunit_every - 1 - (int32_t)(j % (uint32_t)reunit_every));
             if (k > 0) {
-                HIP_TRY(launch_team_sweeps(ens(), team_width(), k, nor, seed, reunit_every, site,
-                                           flags, hist, d_qs(), d_teams(), spin_limit, stream));
+                HIP_TRY(launch(k, reunit_every, site, flags, hist));
             } else {
                 k = 1;
-                HIP_TRY(launch_team_sweeps(ens(), team_width(), 1, nor, seed, 0, false, 16,
-                                           nullptr, d_qs(), d_teams(), spin_limit, stream));
+                HIP_TRY(launch(1, 0, false, 16, nullptr));
                 HIP_TRY(reunitarize_launch());
                 if (want_p) HIP_TRY(plaquette_launch());
                 if (want_l) HIP_TRY(polyakov_launch());
@@ -632,8 +643,8 @@ public:
         return SU2_OK;
     }
 
-    // After queue launches: wait for the stream and report a wait that ran
-    // out (the flag is cleared).
+    // After queue and team launches: wait for the stream and report a wait that
+    // ran out (the flag is cleared).
     int check_queue()
     {
         if (!queue_used) return SU2_OK;
@@ -644,11 +655,13 @@ public:
         if (err) {
             HIP_TRY(launch_set_counter(ens(), 0, 0, 16, stream, d_qs()));
             HIP_TRY(hipStreamSynchronize(stream));
-            return fail(SU2_EHIP, err == 1u ? "work-queue launch: a bounded wait ran out of polls; "
-                                              "the sweeps since the last check are invalid"
-                                            : "work-queue launch: an XCD queue was not served "
-                                              "(too few workgroups); the sweeps since the last "
-                                              "check are invalid");
+            const char *what =
+                err == 1u   ? "work-queue launch: a bounded wait ran out of polls"
+                : err == 2u ? "work-queue launch: an XCD queue was not served (too few workgroups)"
+                : err == 3u ? "team launch: a bounded wait between its workgroups ran out of polls"
+                            : "team launch: a lattice found no team of workgroups";
+            return fail(SU2_EHIP,
+                        std::string(what) + "; the sweeps since the last check are invalid");
         }
         return SU2_OK;
     }
