@@ -536,8 +536,8 @@ public:
     // Whole sweeps by a team of workgroups on one XCD per lattice, where the
     // launch was not set, between the sizes that one workgroup and those that
     // the whole chip runs faster.
-    // ns, meas: sweeps of the call, and what is measured after each.
-    bool team_path(int mode, int32_t ns, int meas) const
+    // ns, reunit_every, meas: sweeps of the call, and what follows each.
+    bool team_path(int mode, int32_t ns, int32_t reunit_every, int meas) const
     {
         if (f64 || !auto_launch || mode == SU2_LEARNED || max_vh > kTeamMaxVh) return false;
         const bool over = mode == SU2_KP_OR;
@@ -546,16 +546,19 @@ public:
             // Four tiles: one workgroup is faster at a measured sweep by itself (us, team /
             // one workgroup: V/2 864 47.6 / 45.4, 1024 47.4 / 45.3; two sweeps 76.0 / 75.4
             // and 70.7 / 76.2) and, while the fourth is hardly filled, at few sweeps with
-            // the Polyakov loop (V/2 800: 2 sweeps 87.1 / 83.3, 8 288 / 285, 12 422 / 420)
+            // the Polyakov loop (V/2 800: 2 sweeps 87.1 / 83.3, 8 288 / 285, 12 422 / 420).
+            // Not with a reunitarisation, which the team shares out (1024 50.8 / 55.5)
             const bool one = !over && max_vh <= 1024u &&
+                             (reunit_every == 0 || reunit_every > ns) &&
                              (max_vh <= 832u && (meas & SU2_MEAS_POLY) ? ns < 12
                                                                        : meas && ns < 2);
             return (over || max_vh >= kTeamHeatbathMinVh) && !one;
         }
         const uint32_t most = !over && max_vh <= kSmallMaxVh ? kTeamLoadSmall : kTeamLoad;
         // (three teams of four on an XCD lose: 24 x 8^3 x 4, four sweeps with over-relaxation,
-        // both measurements and two reunitarisations, teams / passes 371 / 323 us)
-        return (uint64_t)slots * width <= most && (slots < 3 || width < 4) &&
+        // both measurements and two reunitarisations, teams / passes 371 / 323 us; a lone
+        // sweep 84 / 92)
+        return (uint64_t)slots * width <= most && (slots < 3 || width < 4 || ns < 2) &&
                (over || max_vh >= kTeamBatchHeatbathMinVh);
     }
     // one workgroup per 256-link tile of the largest lattice
@@ -714,7 +717,7 @@ public:
         if (cfg.queue && !f64 && !per_pass)
             return enqueue_queue(ns, tab, reunit_every, meas, hist);
         const int gflag = rows_graph ? 8 : 0;
-        if (team_path(mode, ns, hist ? meas : 0) && !(reunit_fused && reunit_every > 0))
+        if (team_path(mode, ns, reunit_every, hist ? meas : 0) && !(reunit_fused && reunit_every > 0))
             return enqueue_team(ns, mode, reunit_every, meas, hist, gflag);
         if (small_path() && !per_pass) {
             const int flags = (hist && (meas & SU2_MEAS_PLAQ) ? 1 : 0) |
