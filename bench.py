@@ -830,18 +830,25 @@ def scale_setting(su2, torch, dev, betas=POLYAKOV_BETAS, therm=300, nmeas=40, ev
             lat.wilson_loops(4, 4)
         dt = (time.perf_counter() - t0) / 5
     out["wilson_4x4_48^4_ms"] = 1e3 * dt
-    # per site and ordered plane (R, T <= 4): 72 quaternion products (16 FMA each), 16
-    # four-term dot products, 40 link loads of 16 B; 12 ordered planes per site
     V = int(np.prod(DIMS))
-    flop = 12 * (72 * 16 + 16 * 4) * 2 * V
-    gathered = 12 * 40 * 16 * V
+    flop, gathered = wilson_work(4)
     out["wilson_4x4_48^4"] = {
-        "fp32_tflops": flop / dt / 1e12, "fp32_frac": flop / dt / 1e12 / FP32_PEAK_TFLOPS,
-        "gathered_bytes_per_site": 12 * 40 * 16, "gathered_tbs": gathered / dt / 1e12,
+        "fp32_tflops": flop * V / dt / 1e12,
+        "fp32_frac": flop * V / dt / 1e12 / FP32_PEAK_TFLOPS,
+        "gathered_bytes_per_site": gathered, "gathered_tbs": gathered * V / dt / 1e12,
         "hbm_algorithmic_frac": 64 * V / dt / 1e9 / HBM_PEAK_GBS,
-        "note": "one thread per site and plane; the links of each stage of the loop lines "
-                "are gathered together (480 16-byte gathers per site, served by L1/L2)"}
+        "note": "one thread per site and plane mu < nu; the links of each stage of the loop "
+                f"lines are gathered together ({gathered // 16} 16-byte gathers per site, served "
+                "by L1/L2)"}
     return out
+
+
+def wilson_work(n):
+    """FP32 operations and gathered bytes per site of the loops R, T <= n: six planes mu < nu, in
+    each A and B (n - 1 products), C and D (n (n - 1)), two products and a four-term dot
+    product per loop (16 and 4 FMAs), and n (2 n + 1) + n link loads of 16 bytes."""
+    products = 2 * (n - 1) + 2 * n * (n - 1) + 2 * n * n
+    return 6 * (16 * products + 4 * n * n) * 2, 6 * (n * (2 * n + 1) + n) * 16
 
 
 def cpu_baseline(sample_sweeps=5):
