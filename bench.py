@@ -9,7 +9,9 @@ time of the same sweeps with a separate reunitarisation pass and plaquette is
 reported beside it).  Throughput
 = link updates per second (4 V per sweep) with the links resident in HBM.
 Other workloads (4^4, beta scans, 32^3 x Nt with the Polyakov loop, the
-batched learned-vs-plain comparison) are reported in the same JSON line.
+batched learned-vs-plain comparison) are reported in the details on stderr;
+the JSON line on stdout holds the headline, its roofline and the two proposals'
+rates.
 
 The roofline object reports the dominant kernel (the heat-bath pass):
 128 algorithmic bytes per link update (the pass reads U_nu, nu != mu, at both
@@ -887,6 +889,29 @@ def host_cpu():
             "usable_cpus": len(os.sched_getaffinity(0))}
 
 
+def result_line(out):
+    """The line on stdout: the headline, its roofline and the proposals' rates, short enough to survive a cut to the
+    last lines of the output.  Everything measured goes to stderr."""
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+            "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config",
+            "plaquette_mean_last_half", "autotuned_us_per_sweep", "launch")
+    line = {k: out[k] for k in keys}
+    roof = ("bound", "achieved", "peak", "unit", "frac", "traffic", "kernel", "avg_launch_us",
+            "floor_us", "frac_of_floor")
+    line["roofline"] = {k: out["roofline"][k] for k in roof}
+    if "learned_vs_plain" in out:
+        lp = out["learned_vs_plain"]
+        line["learned_vs_plain"] = {
+            "plain_link_updates_per_s": lp["plain"]["link_updates_per_s"],
+            "learned_link_updates_per_s": lp["learned"]["link_updates_per_s"],
+            "learned_over_plain_effective": lp["learned_over_plain_effective"],
+            "learned_overrelaxed_over_plain_overrelaxed_effective":
+                lp["learned_overrelaxed_over_plain_overrelaxed_effective"]}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -1099,7 +1124,8 @@ def main():
     if not args.no_cpu_baseline:
         print("[bench] CPU oracle baseline", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline()
-    print(json.dumps(out), flush=True)
+    print("[bench] details: " + json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(result_line(out)), flush=True)
 
 
 if __name__ == "__main__":
