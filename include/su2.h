@@ -96,7 +96,7 @@ int su2_init_ext(su2_ctx **out, const int32_t dims[4], double beta, uint64_t see
  * L_mu(x, n) = U_mu(x) U_mu(x+mu) ... U_mu(x+(n-1)mu), R = 1..rmax,
  * T = 1..tmax; W(1,1) is the plaquette.  Per-site values FP32, sums FP64
  * (deterministic order).  Synchronous; the first call allocates a device
- * buffer of 160 KB that the context keeps.
+ * buffer of 62 KB that the context keeps.
  * SU2_EINVAL unless 1 <= rmax, tmax <= 4 and both are below every extent;
  * SU2_ESTATE on an FP64 context.  out: host double[rmax * tmax]. */
 int su2_wilson_loops(su2_ctx *ctx, int rmax, int tmax, double *out);
@@ -134,8 +134,9 @@ int su2_destroy(su2_ctx *ctx);
  * sweep, then n_or microcanonical over-relaxation sweeps (su2_set_hb_overrelax;
  * default 1) in the same order, each link U -> U~^+ U^+ U~^+ with U~ = V/|V|
  * (keeps (1/2)Tr(U V) and the Haar measure, draws no randoms; V = 0 leaves
- * U), always as per-pass launches.  The sweep index advances by nsweeps
- * (one per compound sweep).  FP64 contexts: SU2_KP only. */
+ * U), as per-pass launches or, where no launch is set, small lattices' teams,
+ * never as the whole-sweep or work-queue launch.  The sweep index advances by
+ * nsweeps (one per compound sweep).  FP64 contexts: SU2_KP only. */
 int su2_heatbath_sweep(su2_ctx *ctx, int32_t nsweeps, int mode);
 
 /* Enqueue nsweeps sweeps and measure after each one.  reunit_every > 0
@@ -188,8 +189,8 @@ int su2_plaquette(su2_ctx *ctx, double *out);
 int su2_polyakov(su2_ctx *ctx, double *out_signed, double *out_abs);
 
 /* Copy links to / from the host exchange layout float[V][4][4] (host pointer,
- * 64*V bytes).  Synchronous.  The first call allocates a device staging
- * buffer of at most 32 MB that the context keeps. */
+ * 64*V bytes).  Synchronous.  Past 4096 sites (FP64 links: 1400) the first call
+ * allocates a device staging buffer of at most 32 MB that the context keeps. */
 int su2_get_links(su2_ctx *ctx, float *host);
 int su2_set_links(su2_ctx *ctx, const float *host);
 

@@ -8,10 +8,12 @@
 
 #include <hip/hip_runtime.h>
 
-// Products and sums are fused into FMAs only within one source expression
-// (never across statements after inlining), so every kernel built on these
-// functions rounds the update identically whatever surrounds it: the plain and
-// the LDS-staged pass give bit-identical links.
+// `contract(on)` asks for FMAs within one source expression only.  The build's
+// -ffp-contract=fast lets the back end go further: it also contracts across
+// statements after inlining.  The kernels built on these functions round an update
+// alike because they inline the same expressions, and tests compare their links bit
+// for bit; a kernel that splits an expression has to write out the FMAs that the
+// whole one contracted to.
 #pragma clang fp contract(on)
 #include <stdint.h>
 

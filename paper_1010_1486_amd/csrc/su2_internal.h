@@ -212,14 +212,16 @@ __host__ __device__ inline uint32_t queue_sweep_last(const QueuePlan &p, uint32_
 // 1024 threads, 2 sites per thread).
 constexpr uint32_t kSmallMaxVh = 2048;
 // Largest V/2 whose heat-bath sweeps keep the field in LDS (three threads per
-// link, at most 960, and 208 bytes of LDS per half-site within 64 KiB).
+// link, at most 960, and 208 bytes of LDS per half-site within 64 KiB); large
+// batches of them do not, see tiny_fits.
 constexpr uint32_t kTinyMaxVh = 312;
 // V/2 of the lattices whose sweeps a team of workgroups on one XCD runs.  Up to 12
 // tiles of 256 links; with more the barriers cost what the launches do (us per
 // sweep, team / pass launches: 8^4 26.2 / 28.3, 16 x 16 x 8 x 4 27.2 / 29.4, a lone sweep
 // of it 44.9 / 43.2, 10^4 31.1 / 30.0).  The heat bath alone only past three tiles, up
 // to which one workgroup is as fast (one workgroup / team, with both measurements:
-// 6^4 26.7 / 28.4, 8^3 x 4 32.1 / 25.5).
+// 6^4 26.7 / 28.4, 8^3 x 4 32.1 / 25.5), and with four tiles not in every short call, see
+// Ensemble::team_path.
 constexpr uint32_t kTeamMaxVh = 3072, kTeamHeatbathMinVh = 769;
 // Batches up to this many of the teams' workgroups on an XCD, as they slow each
 // other down: in the heat bath up to V/2 2048 kTeamLoadSmall, where one workgroup per
@@ -366,7 +368,7 @@ constexpr int kNNParams = 2671;
 constexpr int kNNPart = kNNParams + 1;  // a workgroup's partial sums: gradient, loss
 constexpr int kNNTile = 64;             // samples a workgroup takes at a time
 // Workgroups of a training step: one per 64 samples, at most 512 (two per CU,
-// 12 MB of partial sums), which then take several tiles each.
+// 11 MB of partial sums), which then take several tiles each.
 inline int nn_parts(int batch) { return std::min((batch - 1) / kNNTile + 1, 512); }
 
 struct NNBuffers {

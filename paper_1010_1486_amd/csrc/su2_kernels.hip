@@ -831,7 +831,8 @@ __device__ __forceinline__ TinyRand tiny_trial(const U4 &w)
 {
     const float r1 = u01(w.a), r2 = u01(w.b), r3 = u01(w.c), r4 = u01(w.d);
     const float c = hw_cos_rev(r2), l3 = hw_log2(r3);
-    // the FMAs that sample_delta's expressions contract to
+    // the FMAs that sample_delta's expressions contract to in the pass kernels, written
+    // out: the compiler contracts across statements, so that it would form others here
     return TinyRand{fmaf(c * c, l3, hw_log2(r1)), r4 * r4, fmaf(-hw_sqrt(r1), c, 1.0f), l3};
 }
 
@@ -894,7 +895,7 @@ __device__ __forceinline__ Q lq(const float4 *p)
 }
 __device__ __forceinline__ float4 f4(const Q &q) { return float4{q.w, q.x, q.y, q.z}; }
 
-// A site's half-site neighbours, 16 bits each.
+// A site's half-site neighbours.
 struct TinySite {
     uint32_t p[4], m[4];
     uint32_t xodd;

@@ -1132,8 +1132,9 @@ int Ensemble::autotune(const char *cache_path, int mode, double *best_us)
         return set_launch(best.block, best.flags, best.tz, best.tt, best.grid);
     }
     // Snapshot of everything the trial sweeps change: the links and each
-    // replica's counters, accumulators (accept statistics included) and
-    // result slots.  Every failure below still restores it.
+    // replica's counters and accumulators (accept statistics included; the result
+    // slots are written by the call that reads them).  Every failure below still
+    // restores it.
     const size_t rb = rep_bytes();
     std::vector<void *> saved(n, nullptr);
     void *rep_saved = nullptr;
