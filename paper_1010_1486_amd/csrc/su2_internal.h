@@ -343,10 +343,11 @@ hipError_t launch_wilson(const Ens &e, int n, double *work, double **sums, hipSt
 // Workgroups of `block` threads of the queue kernel the device holds at once.
 uint32_t queue_resident_grid(int block, bool learned);
 // which: 1 set sweep, 2 set meas_idx, 4 zero all accumulators, 8 zero counts,
-// 16 zero the state of queue and team launches (done counters; qs ticket, error
-// and team; the sums), 32 set graph_row.
+// 16 zero the state of queue and team launches (done counters; qs ticket and
+// error; the teams; the sums), 32 set graph_row.
 hipError_t launch_set_counter(const Ens &e, uint32_t sweep, uint32_t meas, int which,
-                              hipStream_t stream, QueueState *qs = nullptr);
+                              hipStream_t stream, QueueState *qs = nullptr,
+                              TeamState *teams = nullptr);
 // results[R_COUNTS..] = proposals, accepts (as uint64); reset if asked.
 hipError_t launch_counts(const Ens &e, int reset, hipStream_t stream);
 // Sites [s0, s0 + n) of replica r between the device layout (dev64: FP64

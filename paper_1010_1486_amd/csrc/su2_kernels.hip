@@ -631,15 +631,17 @@ __global__ __launch_bounds__(kBuckets) void counts_kernel(const Rep *__restrict_
 
 __global__ __launch_bounds__(kBuckets) void set_counter_kernel(const Rep *__restrict__ reps,
                                                                uint32_t sweep, uint32_t meas,
-                                                               int which, QueueState *qs)
+                                                               int which, QueueState *qs,
+                                                               TeamState *teams)
 {
     const Rep &R = reps[blockIdx.z];
     if ((which & 16) && threadIdx.x == 0) {
         R.cnt->done = 0u;
+        TeamState *const ts = teams + blockIdx.z;
+        ts->target = ts->join = ts->size = ts->bar = 0u;
         if (qs && blockIdx.z == 0) {
             for (int k = 0; k < kMaxQueues; ++k) qs->ticket[k][0] = 0u;
             qs->error = 0u;
-            qs->team.target = qs->team.join = qs->team.size = qs->team.bar = 0u;
         }
     }
     if (which & 16)  // a launch that gave up leaves sums behind
@@ -2059,10 +2061,10 @@ hipError_t launch_counts(const Ens &e, int reset, hipStream_t stream)
 }
 
 hipError_t launch_set_counter(const Ens &e, uint32_t sweep, uint32_t meas, int which,
-                              hipStream_t stream, QueueState *qs)
+                              hipStream_t stream, QueueState *qs, TeamState *teams)
 {
     hipLaunchKernelGGL(set_counter_kernel, dim3(1, 1, e.nrep), dim3(kBuckets), 0, stream, e.reps,
-                       sweep, meas, which, qs);
+                       sweep, meas, which, qs, teams);
     return hipGetLastError();
 }
 

@@ -291,8 +291,9 @@ public:
     void *stage = nullptr;          // staging of the host exchange (device, owned)
     size_t stage_bytes = 0;
     double *wilson_work = nullptr;  // partial sums of the Wilson loops (device, owned)
-    uint2 *amap = nullptr;  // XCD-affine pass map (device, owned), see Ens
+    uint2 *amap = nullptr;  // XCD-affine pass map (device), see Ens
     uint32_t amap_len = 0;
+    bool own_amap = false;  // amap is an allocation of its own, not in the scratch
     Rep rep0{};  // the first replica's descriptor, as uploaded
     LaunchCfg cfg;
     // No launch configuration was set: batches of replicas with fields up to
@@ -435,12 +436,13 @@ public:
             h[r].qfirst = 0u;
             h[r].orw = orw;
         }
-        if (amap) {
+        if (amap && own_amap) {
             HIP_TRY(hipStreamSynchronize(stream));  // no pass may still read it
             (void)hipFree(amap);
         }
         amap = nullptr;
         amap_len = 0;
+        std::vector<uint2> m;
         if (n > 1 && !f64 && (cfg.affine || (auto_launch && max_vh <= kAffineMaxVh))) {
             // replicas spread over the XCDs by size (as the work queue); the
             // blocks of replica r go, in order, to workgroups b = slot * nq + x
@@ -455,14 +457,10 @@ public:
             // unasked, only where the fullest XCD has at most a tenth more than its share
             const uint64_t all = std::accumulate(qslots.begin(), qslots.end(), (uint64_t)0);
             if (cfg.affine || 10ull * nq * maxlen <= 11ull * all) {
-                std::vector<uint2> m((size_t)nq * maxlen, uint2{0xFFFFFFFFu, 0u});
+                m.assign((size_t)nq * maxlen, uint2{0xFFFFFFFFu, 0u});
                 for (int r = 0; r < n; ++r)
                     for (uint32_t k = 0; k < nblocks[r]; ++k)
                         m[(size_t)(qfirst[r] + k) * nq + qof[r]] = uint2{(uint32_t)r, k};
-                HIP_TRY(hipMalloc(&amap, m.size() * sizeof(uint2)));
-                HIP_TRY(hipMemcpy(amap, m.data(), m.size() * sizeof(uint2),
-                                  hipMemcpyHostToDevice));
-                amap_len = (uint32_t)m.size();
             }
         }
         if (cfg.queue) {
@@ -507,7 +505,28 @@ public:
                 const uint32_t end = r + 1 < n ? first_block[r + 1] : total_blocks;
                 for (uint32_t b = first_block[r]; b < end; ++b) map[b] = (uint32_t)r;
             }
+            // The affine map follows the workgroup map in one copy, where the room of the
+            // two maps (sized for 64-thread workgroups) and the work queue leave it place
+            // (creating 8 x 16^4 takes 116 us, 139 with a copy and an allocation of its own)
+            const size_t at = align_up(map.size() * 4, sizeof(uint2)), bytes = m.size() * sizeof(uint2);
+            const bool own = cfg.queue || at + bytes > 2 * bmap_bytes(n, dims);
+            if (!m.empty() && !own) {
+                map.resize((at + bytes) / 4);
+                std::memcpy(&map[at / 4], m.data(), bytes);
+            }
             HIP_TRY(hipMemcpy(d_bmap(), map.data(), map.size() * 4, hipMemcpyHostToDevice));
+            if (!m.empty()) {
+                void *p = reinterpret_cast<unsigned char *>(d_bmap()) + at;
+                if (own) {
+                    HIP_TRY(hipMalloc(&p, bytes));
+                    const hipError_t e = hipMemcpy(p, m.data(), bytes, hipMemcpyHostToDevice);
+                    if (e != hipSuccess) (void)hipFree(p);
+                    HIP_TRY(e);
+                }
+                amap = static_cast<uint2 *>(p);
+                own_amap = own;
+                amap_len = (uint32_t)m.size();
+            }
         }
         return SU2_OK;
     }
@@ -517,7 +536,7 @@ public:
         int *d = nullptr;
         HIP_TRY(hipMalloc(&d, n * sizeof(int)));
         hipError_t e = hipMemcpy(d, starts.data(), n * sizeof(int), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = launch_set_counter(ens(), 0, 0, 7 | 16, stream, d_qs());
+        if (e == hipSuccess) e = launch_set_counter(ens(), 0, 0, 7 | 16, stream, d_qs(), d_teams());
         if (e == hipSuccess)
             e = f64 ? launch_init64(ens(), starts[0], seed, stream) : launch_init(ens(), d, seed, stream);
         if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -656,7 +675,7 @@ public:
         HIP_TRY(hipStreamSynchronize(stream));
         queue_used = false;
         if (err) {
-            HIP_TRY(launch_set_counter(ens(), 0, 0, 16, stream, d_qs()));
+            HIP_TRY(launch_set_counter(ens(), 0, 0, 16, stream, d_qs(), d_teams()));
             HIP_TRY(hipStreamSynchronize(stream));
             const char *what =
                 err == 1u   ? "work-queue launch: a bounded wait ran out of polls"
@@ -1043,7 +1062,7 @@ public:
         if (stream) (void)hipStreamSynchronize(stream);
         if (own_pool && pool) (void)hipFree(pool);
         if (own_scratch && scratch) (void)hipFree(scratch);
-        if (amap) (void)hipFree(amap);
+        if (amap && own_amap) (void)hipFree(amap);
         amap = nullptr;
         if (wilson_work) (void)hipFree(wilson_work);
         wilson_work = nullptr;
@@ -1846,10 +1865,7 @@ int su2_batch_init(su2_batch **out, int32_t n, const int32_t *dims, const double
     E.bmap_off = Ensemble::descr_bytes(n);
     E.qmap_off = E.bmap_off + Ensemble::bmap_bytes(n, E.dims);
     E.rep_off = E.qmap_off + Ensemble::bmap_bytes(n, E.dims);
-    if (n > 1) e = hipMemsetAsync(E.d_teams(), 0, Ensemble::team_bytes(n), E.stream);
-    if (e != hipSuccess) rc = fail(SU2_EHIP, std::string("teams: ") + hipGetErrorString(e));
-    if (e != hipSuccess || (rc = E.upload()) ||
-        (rc = E.init(std::vector<int>(starts, starts + n)))) {
+    if ((rc = E.upload()) || (rc = E.init(std::vector<int>(starts, starts + n)))) {
         E.release();
         delete b;
         return rc;

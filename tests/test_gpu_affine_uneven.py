@@ -48,3 +48,24 @@ def test_su3_orders(su2, dims, n):
             np.testing.assert_array_equal(lat.heatbath_sweep(2, 2, history=True), h[:, r])
             lat.overrelax(1)
             np.testing.assert_array_equal(lat.get_links(), links[r])
+
+
+def test_switching_between_affine_launches(su2):
+    """The affine map lies in the batch's scratch (128- and 256-thread workgroups, the unset launch)
+    or in an allocation of its own (64 threads, with the work queue's flag), and moves between
+    them."""
+    announce("batch order: switching launches")
+    dims = [A, B] * 4
+    betas = np.linspace(1.5, 3.0, len(dims))
+    with su2.Batch(dims, betas, su2.SU2_HOT, 11) as a, su2.Batch(dims, betas, su2.SU2_HOT, 11) as b:
+        b.set_launch(256, 1 | 2 | 4)
+        unset = a.launch()
+        for launch in ((64, 64 | 4), (256, 257), (64, 64 | 4, 1, 1, 64), (128, 64 | 4),
+                       (256, 64 | 8), (256, 64 | 4), (64, 66 | 4), (256, 1 | 4), (256, 257)):
+            a.set_launch(*launch)
+            for x in (a, b):
+                x.sweep(1)
+                x.sweep(1, su2.SU2_KP_OR)
+        assert a.launch() == unset
+        for r in range(len(dims)):
+            np.testing.assert_array_equal(a.get_links(r), b.get_links(r))
