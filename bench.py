@@ -890,8 +890,8 @@ def host_cpu():
 
 
 def result_line(out):
-    """The line on stdout: the headline, its roofline and the proposals' rates, short enough to survive a cut to the
-    last lines of the output.  Everything measured goes to stderr."""
+    """The line on stdout: the headline, its roofline and the proposals' rates, short enough to
+    survive a cut to the last lines of the output.  Everything measured goes to stderr."""
     keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
             "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config",
             "plaquette_mean_last_half", "autotuned_us_per_sweep", "launch")
